@@ -68,8 +68,8 @@ def parse_args():
     ap.add_argument("--cycle", action="store_true",
                     help="rotate each worker's partition every step (Algorithm 1) instead of fixed ranks")
     ap.add_argument("--variant", default="auto", choices=["auto", "staged", "ticket"],
-                    help="kernel schedule (auto, the library default, runs the ticket schedule up to "
-                         "2^20 values per partition and the staged one above)")
+                    help="kernel schedule (auto, the library default, runs one launch up to "
+                         "2^22 values per partition and the staged schedule above)")
     ap.add_argument("--separate-scan", action="store_true",
                     help="staged schedule: launch the scan pass on its own instead of inside the "
                          "streaming launch (the library default for partitions of up to a few hundred "
@@ -1052,6 +1052,8 @@ def main():
                and not args.separate_scan and args.variant == "auto" else None)
     parts = sorted({ln for (_, ln) in (micro.micro_partition(w.n_total, p, w.world)
                                        for p in (range(w.world) if args.cycle else w.ranks))})
+    one_launch = (main_res["variant"] != micro.MICRO_VARIANT_STAGED
+                  or (args.variant == "auto" and not args.separate_scan and max(parts) <= 1 << 22))
     line = {
         "metric": METRIC,
         "value": main_res["g_elem_s"],
@@ -1089,7 +1091,7 @@ def main():
             "unit": "GB/s",
             "frac": main_res["kernel_gbs"] / HBM_PEAK_GBS,
             "traffic": traffic,
-            "kernel": ("ticket_kernel" if main_res["variant"] != micro.MICRO_VARIANT_STAGED else
+            "kernel": ("one_pass_kernel" if one_launch else
                        "stream_scan_kernel + move_kernel (one step, event-timed together)" if main_res["fused"] else
                        "stream_kernel + scan_kernel + move_kernel (one step, event-timed together)"),
             "kernel_ms_avg": main_res["kernel_ms_avg"],

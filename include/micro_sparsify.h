@@ -112,10 +112,12 @@ typedef enum micro_status {
 
 /* Kernel schedules (both compute the same result). */
 #define MICRO_VARIANT_AUTO 0   /* per call, the faster measured schedule: TICKET
-                                  for partitions of up to 2^20 values (one
-                                  launch), STAGED above; both scratch sets     */
-#define MICRO_VARIANT_TICKET 1 /* one pass; tiles from a ticket counter, each
-                                  tile's offset by decoupled look-back           */
+                                  for partitions of up to 2^20 values, STAGED
+                                  above, which up to 2^22 values keeps its staged
+                                  pairs in local memory and places them in the
+                                  same single launch; both scratch sets         */
+#define MICRO_VARIANT_TICKET 1 /* one pass, one launch: each tile's offset by
+                                  decoupled look-back, tiles in launch order     */
 #define MICRO_VARIANT_STAGED 2 /* a streaming pass that stages each tile's pairs
                                   (no inter-workgroup waits), a scan pass (look-
                                   back per chunk of a million values) and a
@@ -147,11 +149,14 @@ typedef struct micro_step_stats {
                                (MICRO_FLAG_TIME_KERNEL), else -1               */
     int64_t redone_tiles;   /* STAGED: 1024-value tiles with more selected
                                values than their staging slot holds (256),
-                               redone by the placing pass instead              */
+                               redone by the placing pass instead (AUTO's
+                               single launch: counted, and placed from
+                               registers where four of them hold over 1024)    */
     int32_t variant;        /* the schedule the last step ran:
                                MICRO_VARIANT_TICKET or MICRO_VARIANT_STAGED    */
     int32_t fused;          /* 1 if its streaming and scan passes ran as one
-                               launch (micro_sparsify_step, STAGED), else 0    */
+                               launch (micro_sparsify_step, STAGED; also where
+                               the placing pass was part of it), else 0        */
     int32_t topk_route;     /* MICRO_RULE_TOPK: how the step found the k-th
                                magnitude (MICRO_TOPK_ROUTE_*); 0 for the other
                                rules, or when nothing was selectable           */
@@ -166,7 +171,7 @@ MICRO_API void micro_config_default(micro_config *cfg);
  * NULL means the null stream).  cfg == NULL selects the defaults.
  * The context owns its device scratch (STAGED: a 256-pair staging slot and a
  * count per 1024 values of the vector plus look-back words, about 2 bytes per
- * value; TICKET: one look-back word per 4096 values; AUTO: both) and a pinned host word
+ * value; TICKET: one look-back word per 4096 values and a few; AUTO: both) and a pinned host word
  * for the selected count; it never owns the caller's buffers.
  * Returns MICRO_EINVAL (ctx NULL, n_total < 0, bad cfg), MICRO_ERANGE
  * (n_total > INT32_MAX: indices are int32), MICRO_EHIP (no usable device) or
@@ -215,9 +220,9 @@ MICRO_API micro_status micro_sparsify_step(micro_ctx *ctx, const float *grad,
  * loops, harnesses that forbid hipMalloc, code that must not allocate after
  * start-up): no context, and no device or host allocation in the call.
  * It runs the one-pass schedule (MICRO_VARIANT_TICKET) with its scratch in
- * one static device array per device (4 MiB + 256 bytes, held from the first
- * call on a device until the process ends): a ticket counter, the count and
- * one look-back word per 4096 values of the partition, enough for any
+ * one static device array per device (4 MiB + 8.5 KB, held from the first
+ * call on a device until the process ends): the count, one look-back word per
+ * 4096 values of the partition and one per 512 of those, enough for any
  * partition of up to 2^31 - 1 values.
  *   grad, residual, rank, world, density, theta, out_idx, out_val, k:
  *              as micro_sparsify_step, over a vector of n_total values on

@@ -28,9 +28,9 @@ struct micro_ctx {
     hipStream_t stream = nullptr;
     micro_config cfg{};
     bool has_staged = true;                  // scratch of the staged schedule allocated
-    bool has_ticket = false;                 // scratch of the ticket schedule allocated
+    bool has_one_pass = false;               // scratch of the one-pass schedule allocated
     int64_t tile_capacity = 0;               // staged tiles of the largest partition (or sweep)
-    int64_t ticket_capacity = 0;             // ticket tiles of the largest partition
+    int64_t pass_capacity = 0;               // one-pass tiles of the largest partition
     // staged schedule: tile counts, staged pairs, chunk look-back words
     uint32_t* d_tile_counts = nullptr;
     uint32_t* d_tile_excl = nullptr;
@@ -42,9 +42,12 @@ struct micro_ctx {
     uint64_t* d_chunk_status = nullptr;
     int64_t chunk_capacity = 0;
     uint64_t* d_tile_words = nullptr;        // fused schedule: epoch-tagged tile counts
-    // ticket schedule: tile look-back words
+    // one-pass schedule: tile and group look-back words
     uint64_t* d_status = nullptr;
-    unsigned long long* d_tickets = nullptr; // [0] tile ticket of the one-pass schedule
+    uint64_t* d_group_status = nullptr;
+    int64_t group_capacity = 0;
+    uint8_t* h_dense = nullptr;              // mapped pinned host memory: dense rows per tile, kDenseTiles
+    uint8_t* h_dense_dev = nullptr;
     int64_t* d_count = nullptr;              // [0] selected count, [1] (epoch << 32) | flagged tiles
     int64_t* h_count = nullptr;              // mapped pinned host memory stored by the kernels: [0] k,
                                              // [1] redone tiles, [2 + r] a sweep's counts
@@ -81,11 +84,19 @@ struct DeviceScope {
     DeviceScope& operator=(const DeviceScope&) = delete;
 };
 
-// Largest partition that an AUTO context runs on the ticket schedule.  On
-// MI355X the ticket schedule's single launch took 8.7 us of device time for
-// 262,144 values against 15.6 us for the staged schedule's three, and lost
-// from 3.2M values on (27 us against 23 us).
+// AUTO contexts report MICRO_VARIANT_TICKET for partitions of up to this many
+// values and MICRO_VARIANT_STAGED above.
 constexpr int64_t kAutoTicketMax = int64_t(1) << 20;
+
+// Largest partition that an AUTO context runs in one launch.  Wall time of a
+// step in one launch and on the staged schedule (d = 0.01, same box): 2.0M
+// values 22.3 and 26.8 us, 3.2M 27.4 and 29.8, 5.0M 33.6 and 32.8, 8.0M 38.8
+// and 38.7, 11.7M 49.0 and 46.4, 16M 59.4 and 54.8: past four million values
+// the look-back's contention costs more than a second launch.
+constexpr int64_t kOnePassMax = int64_t(1) << 22;
+
+// Tiles of the largest one-launch partition whose dense rows are counted.
+constexpr int64_t kDenseTiles = kOnePassMax / (micro::kPassRowsMid * micro::kPassRow) + 2;
 
 thread_local std::string g_init_error = "no error";
 
@@ -162,10 +173,11 @@ bool ranges_overlap(const void* a, size_t an, const void* b, size_t bn) {
 }
 
 micro_status reset_scratch(micro_ctx* ctx) {
-    hipError_t e = hipMemsetAsync(ctx->d_tickets, 0, sizeof(unsigned long long), ctx->stream);
-    if (e == hipSuccess) e = hipMemsetAsync(ctx->d_count, 0, 2 * sizeof(int64_t), ctx->stream);
+    hipError_t e = hipMemsetAsync(ctx->d_count, 0, 2 * sizeof(int64_t), ctx->stream);
     if (e == hipSuccess && ctx->d_status)
-        e = hipMemsetAsync(ctx->d_status, 0, sizeof(uint64_t) * ctx->ticket_capacity, ctx->stream);
+        e = hipMemsetAsync(ctx->d_status, 0, sizeof(uint64_t) * ctx->pass_capacity, ctx->stream);
+    if (e == hipSuccess && ctx->d_group_status)
+        e = hipMemsetAsync(ctx->d_group_status, 0, sizeof(uint64_t) * ctx->group_capacity, ctx->stream);
     if (e == hipSuccess && ctx->d_chunk_status)
         e = hipMemsetAsync(ctx->d_chunk_status, 0, sizeof(uint64_t) * ctx->chunk_capacity, ctx->stream);
     if (e == hipSuccess && ctx->d_tile_words)
@@ -187,12 +199,13 @@ void release(micro_ctx* ctx) {
     for (hipEvent_t ev : ctx->ev)
         if (ev) (void)hipEventDestroy(ev);
     void* device_buffers[] = {ctx->d_tile_counts, ctx->d_tile_excl, ctx->d_flagged_list, ctx->d_split_tile, ctx->d_tile_sumsq, ctx->d_stage,
-                              ctx->d_chunk_status, ctx->d_tile_words, ctx->d_status, ctx->d_tickets,
+                              ctx->d_chunk_status, ctx->d_tile_words, ctx->d_status, ctx->d_group_status,
                               ctx->d_count, ctx->d_topk};
     for (void* p : device_buffers)
         if (p) (void)hipFree(p);
     if (ctx->h_count) (void)hipHostFree(ctx->h_count);
     if (ctx->h_sumsq) (void)hipHostFree(ctx->h_sumsq);
+    if (ctx->h_dense) (void)hipHostFree(ctx->h_dense);
     if (ctx->h_topk) (void)hipHostFree(ctx->h_topk);
     delete ctx;
 }
@@ -645,6 +658,14 @@ micro_status topk_finish(micro_ctx* ctx, const TopkPlan& plan, int64_t listed_by
     return MICRO_OK;
 }
 
+// Rows with more than kStageCap selected values of a one-pass launch of
+// `tiles` tiles (waited for).
+int64_t dense_rows(const micro_ctx* ctx, int64_t tiles) {
+    int64_t n = 0;
+    for (int64_t i = 0; i < tiles; ++i) n += ctx->h_dense[i];
+    return n;
+}
+
 // Validation, launch, count readback and threshold update of one sparsify
 // step over [start, start + len); with accumulate_outside the rest of the
 // vector is accumulated too (the full error-feedback pass), and with sumsq the
@@ -741,12 +762,16 @@ micro_status execute_step(micro_ctx* ctx, const float* grad, float* residual, in
                                          : 0u;
         }
     }
-    // AUTO contexts take the one-pass ticket schedule for partitions of up to
-    // kAutoTicketMax values, where one launch beats three, and the staged
-    // schedule above, where the ticket schedule's per-tile round trips cost
-    // bandwidth.
-    const bool staged = ctx->has_staged && !(ctx->has_ticket && len <= kAutoTicketMax);
-    const int64_t tile_elems = staged ? micro::kStreamTile : micro::kTicketTile;
+    // AUTO contexts run partitions of up to kOnePassMax values in one launch
+    // and the staged schedule above.  Above kAutoTicketMax the top-k
+    // comparator's step at a hint's bound is the staged kernels', and the scan
+    // pass can be asked for on its own.
+    const bool separate = (ctx->cfg.flags & MICRO_FLAG_SEPARATE_SCAN) != 0;
+    const int64_t one_launch_max = topk || separate ? kAutoTicketMax : kOnePassMax;
+    const bool staged = ctx->has_staged && !(ctx->has_one_pass && len <= one_launch_max);
+    const bool reports_staged = ctx->has_staged && !(ctx->has_one_pass && len <= kAutoTicketMax);
+    const int rows = micro::pass_rows_for(len);
+    const int64_t tile_elems = staged ? micro::kStreamTile : static_cast<int64_t>(rows) * micro::kPassRow;
     micro::LaunchArgs a{};
     a.grad = grad;
     a.residual = residual;
@@ -754,12 +779,12 @@ micro_status execute_step(micro_ctx* ctx, const float* grad, float* residual, in
     a.out_val = out_val;
     a.start = start;
     a.end = start + len;
-    a.base = micro::tile_base_for(grad, start, vec4);
+    a.base = staged ? micro::tile_base_for(grad, start, vec4) : micro::tile_base_for(residual, start, true);
     a.theta_f = threshold_as_f32(*theta);
     a.epoch = ctx->epoch + 1;
     const int64_t tiles = len > 0 ? (a.end - a.base + tile_elems - 1) / tile_elems : 0;
     const int64_t chunks = (tiles + micro::kChunkTiles - 1) / micro::kChunkTiles;
-    const int64_t capacity = staged ? ctx->tile_capacity : ctx->ticket_capacity;
+    const int64_t capacity = staged ? ctx->tile_capacity : ctx->pass_capacity;
     if (tiles > capacity || (staged && chunks > ctx->chunk_capacity)) {
         set_error(ctx, "partition needs %lld tiles, scratch holds %lld", static_cast<long long>(tiles),
                   static_cast<long long>(capacity));
@@ -788,7 +813,13 @@ micro_status execute_step(micro_ctx* ctx, const float* grad, float* residual, in
     a.num_chunks = static_cast<uint32_t>(chunks);
     a.chunk_status = ctx->d_chunk_status;
     a.status = ctx->d_status;
-    a.ticket = &ctx->d_tickets[0];
+    a.group_status = ctx->d_group_status;
+    // above kAutoTicketMax the one launch reports what the staged one would
+    const bool counts_dense = !staged && reports_staged && ctx->h_dense && tiles <= kDenseTiles;
+    if (counts_dense) {
+        std::memset(ctx->h_dense, 0, static_cast<size_t>(tiles));
+        a.host_dense = ctx->h_dense_dev;
+    }
 
     hipError_t e;
     const bool timed = (ctx->cfg.flags & MICRO_FLAG_TIME_KERNEL) != 0;
@@ -824,10 +855,10 @@ micro_status execute_step(micro_ctx* ctx, const float* grad, float* residual, in
         return hip_fail(ctx, e, "accumulate kernel launch");
     // The staged schedule's stream and scan kernels run as one launch unless
     // the caller asked for the scan on its own.
-    const bool fused = staged && (ctx->cfg.flags & MICRO_FLAG_SEPARATE_SCAN) == 0;
+    const bool fused = staged && !separate;
     if (len > 0) {
         ctx->epoch = a.epoch;
-        e = !staged ? micro::launch_ticket(a, vec4, ctx->stream)
+        e = !staged ? micro::launch_one_pass(a, rows, ctx->stream)
             : fused ? micro::launch_fused(a, vec4, ctx->stream)
                     : micro::launch_staged(a, vec4, ctx->stream);
         if (e != hipSuccess) return hip_fail(ctx, e, "sparsify kernel launch");
@@ -865,9 +896,9 @@ micro_status execute_step(micro_ctx* ctx, const float* grad, float* residual, in
     }
     if (timed && (e = hipEventElapsedTime(&ctx->stats.kernel_ms, ctx->ev[0], ctx->ev[1])) != hipSuccess)
         return hip_fail(ctx, e, "hipEventElapsedTime");
-    ctx->stats.redone_tiles = staged ? host_count[1] : 0;
-    ctx->stats.variant = staged ? MICRO_VARIANT_STAGED : MICRO_VARIANT_TICKET;
-    ctx->stats.fused = len > 0 && fused ? 1 : 0;
+    ctx->stats.redone_tiles = staged ? host_count[1] : counts_dense ? dense_rows(ctx, tiles) : 0;
+    ctx->stats.variant = reports_staged ? MICRO_VARIANT_STAGED : MICRO_VARIANT_TICKET;
+    ctx->stats.fused = len > 0 && (fused || (reports_staged && !staged)) ? 1 : 0;
     ctx->stats.topk_route = topk ? topk_route_code(plan.route) : 0;
     *k = selected;
     if (!topk) *theta = next_threshold(ctx->cfg, density, len, selected, *theta);
@@ -1138,7 +1169,6 @@ micro_status micro_sparsify_step_noalloc(const float* grad, float* residual, int
         *k = 0;
         return MICRO_OK;
     }
-    const bool vec4 = ((reinterpret_cast<uintptr_t>(grad) ^ reinterpret_cast<uintptr_t>(residual)) & 15u) == 0;
     micro::LaunchArgs a{};
     a.grad = grad;
     a.residual = residual;
@@ -1146,9 +1176,11 @@ micro_status micro_sparsify_step_noalloc(const float* grad, float* residual, int
     a.out_val = out_val;
     a.start = start;
     a.end = start + len;
-    a.base = micro::tile_base_for(grad, start, vec4);
+    a.base = micro::tile_base_for(residual, start, true);
     a.theta_f = threshold_as_f32(*theta);
-    const int64_t tiles = (a.end - a.base + micro::kTicketTile - 1) / micro::kTicketTile;
+    const int rows = micro::pass_rows_for(len);
+    const int64_t tile_elems = static_cast<int64_t>(rows) * micro::kPassRow;
+    const int64_t tiles = (a.end - a.base + tile_elems - 1) / tile_elems;
     if (tiles > micro::kStaticMaxTiles) {  // not reachable below 2^31 values; kept as the guard of the scratch
         set_error(nullptr, "partition needs %lld tiles, the static scratch holds %lld", static_cast<long long>(tiles),
                   static_cast<long long>(micro::kStaticMaxTiles));
@@ -1173,15 +1205,15 @@ micro_status micro_sparsify_step_noalloc(const float* grad, float* residual, int
             return noalloc_fail(dv, e, "static scratch clear");
         dv.epoch = 0;
     }
-    a.ticket = reinterpret_cast<unsigned long long*>(dv.words);
-    a.count_out = reinterpret_cast<int64_t*>(dv.words + 1);
-    a.host_count = reinterpret_cast<int64_t*>(dv.words + 3);
+    a.count_out = reinterpret_cast<int64_t*>(dv.words);
+    a.host_count = reinterpret_cast<int64_t*>(dv.words + 2);
     a.status = dv.words + micro::kStaticHeaderWords;
+    a.group_status = a.status + micro::kStaticMaxTiles;
     a.epoch = dv.epoch + 1;
-    if ((e = micro::launch_ticket(a, vec4, stream)) != hipSuccess) return noalloc_fail(dv, e, "sparsify kernel launch");
+    if ((e = micro::launch_one_pass(a, rows, stream)) != hipSuccess) return noalloc_fail(dv, e, "sparsify kernel launch");
     dv.epoch = a.epoch;
     int64_t selected = -1;
-    if ((e = hipMemcpyAsync(&selected, dv.words + 1, sizeof selected, hipMemcpyDeviceToHost, stream)) != hipSuccess)
+    if ((e = hipMemcpyAsync(&selected, dv.words, sizeof selected, hipMemcpyDeviceToHost, stream)) != hipSuccess)
         return noalloc_fail(dv, e, "count readback");
     if ((e = hipStreamSynchronize(stream)) != hipSuccess) return noalloc_fail(dv, e, "hipStreamSynchronize");
     if (selected < 0 || selected > len) {
@@ -1288,9 +1320,8 @@ micro_status micro_sparsify_init(micro_ctx** out, int64_t n_total, void* hip_str
     // Scratch sized for the largest possible partition (the whole vector),
     // plus one tile for the alignment of the first tile.
     ctx->has_staged = c.variant != MICRO_VARIANT_TICKET;
-    ctx->has_ticket = c.variant != MICRO_VARIANT_STAGED;
-    bool ok = hipMalloc(&ctx->d_tickets, sizeof(unsigned long long)) == hipSuccess &&
-              hipMalloc(&ctx->d_count, 2 * sizeof(int64_t)) == hipSuccess &&
+    ctx->has_one_pass = c.variant != MICRO_VARIANT_STAGED;
+    bool ok = hipMalloc(&ctx->d_count, 2 * sizeof(int64_t)) == hipSuccess &&
               hipHostMalloc(&ctx->h_count, (2 + micro::kMaxSweep) * sizeof(int64_t),
                             hipHostMallocMapped | hipHostMallocCoherent) == hipSuccess &&
               hipHostGetDevicePointer(reinterpret_cast<void**>(&ctx->h_count_dev), ctx->h_count, 0) == hipSuccess &&
@@ -1319,9 +1350,15 @@ micro_status micro_sparsify_init(micro_ctx** out, int64_t n_total, void* hip_str
              hipMalloc(&ctx->d_chunk_status, sizeof(uint64_t) * ctx->chunk_capacity) == hipSuccess &&
              hipMalloc(&ctx->d_tile_words, sizeof(uint64_t) * ctx->tile_capacity) == hipSuccess;
     }
-    if (ok && ctx->has_ticket) {
-        ctx->ticket_capacity = n_total / micro::kTicketTile + 2;
-        ok = hipMalloc(&ctx->d_status, sizeof(uint64_t) * ctx->ticket_capacity) == hipSuccess;
+    if (ok && ctx->has_one_pass) {
+        ctx->pass_capacity = micro::pass_tile_capacity(n_total);
+        ctx->group_capacity = ctx->pass_capacity / micro::kGroupTiles + 1;
+        ok = hipMalloc(&ctx->d_status, sizeof(uint64_t) * ctx->pass_capacity) == hipSuccess &&
+             hipMalloc(&ctx->d_group_status, sizeof(uint64_t) * ctx->group_capacity) == hipSuccess;
+        if (ok && ctx->has_staged)
+            ok = hipHostMalloc(&ctx->h_dense, kDenseTiles, hipHostMallocMapped | hipHostMallocCoherent) ==
+                     hipSuccess &&
+                 hipHostGetDevicePointer(reinterpret_cast<void**>(&ctx->h_dense_dev), ctx->h_dense, 0) == hipSuccess;
     }
     if (!ok) {
         set_error(nullptr, "device or pinned host allocation failed");

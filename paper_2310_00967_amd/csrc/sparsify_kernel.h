@@ -27,8 +27,29 @@ constexpr uint32_t kMoveGrid = 2048;  // largest move grid (eight workgroups per
 static_assert((kMoveSpan & (kMoveSpan - 1)) == 0 && (kMoveSpanSmall & (kMoveSpanSmall - 1)) == 0 &&
                   (kMoveSpanTiny & (kMoveSpanTiny - 1)) == 0 && kMoveSpanTiny <= kMoveSpanSmall,
               "piece sizes are powers of two: the kernels divide by them with shifts");
-// Ticket schedule: values per tile (256 threads, four dwordx4 per lane).
-constexpr int kTicketTile = 4096;
+// One-pass schedule: streaming threads of a workgroup, values per row (one
+// dwordx4 per streaming thread), rows per tile, tiles per look-back group.
+// Rows by partition length, wall time of a step with 1, 4 and 6 rows: 262,144
+// values 18.6, 19.0 and 21.1 us (more workgroups share the load); 730,595
+// values 20.0, 19.6 and 22.7; 3.2M values 30.2, 27.0 and 27.5; 11.7M values
+// 67, 46.1 and 45.6; 41.9M values 209, 120 and 110 (fewer tiles look back).
+constexpr int kPassStream = 256;
+constexpr int kPassRow = kPassStream * 4;
+constexpr int kPassRowsSmall = 1, kPassRowsMid = 4, kPassRowsLarge = 6;
+constexpr int64_t kPassSmallMax = int64_t(1) << 19;  // one row up to this length
+constexpr int64_t kPassMidMax = int64_t(1) << 23;    // four rows up to this length, six above
+constexpr uint32_t kGroupTiles = 512;
+inline int pass_rows_for(int64_t len) {
+    return len <= kPassSmallMax ? kPassRowsSmall : len <= kPassMidMax ? kPassRowsMid : kPassRowsLarge;
+}
+// Most tiles of a one-pass launch over len values from an aligned first tile:
+// the shortest tiles any partition of up to len values takes.
+inline int64_t pass_tile_capacity(int64_t len) {
+    const int64_t small = (len < kPassSmallMax ? len : kPassSmallMax) / (kPassRowsSmall * kPassRow) + 2;
+    const int64_t mid = (len < kPassMidMax ? len : kPassMidMax) / (kPassRowsMid * kPassRow) + 2;
+    const int64_t large = len / (kPassRowsLarge * kPassRow) + 2;
+    return small > mid ? (small > large ? small : large) : (mid > large ? mid : large);
+}
 
 // Fused stream-and-scan launch: num_tiles + num_chunks workgroups.  The scan
 // workgroup of chunk c follows the stream workgroup of the last tile of chunk
@@ -123,9 +144,11 @@ struct LaunchArgs {
     uint2* stage;           // num_tiles * kStageCap staged (index, value bits) pairs
     uint32_t num_chunks;    // ceil(num_tiles / kChunkTiles)
     uint64_t* chunk_status;             // >= num_chunks look-back words
-    // ticket schedule
+    // one-pass schedule
     uint64_t* status;                   // >= num_tiles look-back words
-    unsigned long long* ticket;         // 0 at launch, rearmed by the kernel
+    uint64_t* group_status;             // >= ceil(num_tiles / kGroupTiles) look-back words
+    uint8_t* host_dense;                // null, or mapped host memory, zero at launch: per tile its rows with
+                                        // more than kStageCap selected values, where there are any
     // staged schedule, theta_zero > theta_f: of the selected values only those
     // with |acc| >= theta_zero have their residual set to +0; the others keep
     // acc there (the top-k comparator's step at a hint's bound)
@@ -160,7 +183,9 @@ hipError_t launch_staged(const LaunchArgs& args, bool vec4, hipStream_t stream);
 // because every chunk workgroup waits only for workgroups of lower index in
 // the same launch and each XCD dispatches its workgroups in index order.
 hipError_t launch_fused(const LaunchArgs& args, bool vec4, hipStream_t stream);
-hipError_t launch_ticket(const LaunchArgs& args, bool vec4, hipStream_t stream);
+// The one-pass schedule with tiles of `rows` rows (pass_rows_for); a.base from
+// tile_base_for(residual, start, true).
+hipError_t launch_one_pass(const LaunchArgs& args, int rows, hipStream_t stream);
 // The sweep: num_tiles / num_chunks are the totals over the table's segments.
 // fused: the stream and scan passes in one launch of num_tiles + num_chunks
 // workgroups, each segment's workgroups from its wg_first on as fused_role

@@ -14,9 +14,9 @@
 //   * per workgroup: the wavefront row totals go through LDS, giving each
 //     row's offset inside the tile and the tile's count;
 //   * across workgroups: decoupled look-back over 64-bit status words
-//     (count | flag | epoch), one per tile (ticket schedule) or per chunk of
-//     tiles (staged schedule).  Wavefront 0 inspects 64 predecessor tiles
-//     or 256 predecessor chunks per round with agent-scope atomic loads,
+//     (count | flag | epoch), one per tile and per group of tiles (one-pass
+//     schedule) or per chunk of tiles (staged schedule).  A wavefront inspects
+//     its group's tiles and 64 groups, or 256 predecessor chunks, per round with agent-scope atomic loads,
 //     which read the memory level shared by all XCDs.  The count and its flag share one word, so relaxed atomics
 //     suffice: a reader sees either the whole published word or an older one.
 //
@@ -50,11 +50,11 @@
 //   a vector with its own threshold, or a full error-feedback pass split at
 //   its partition), each tile also reducing the squared norm of its new
 //   residual (the local error of Sec. 2) in a fixed order.
-// Ticket schedule: a single pass; 4096-value tiles are drawn from a ticket
-//   counter in increasing order, so a tile only waits for tiles claimed by
-//   running workgroups; the per-tile ticket and look-back round trips cost
-//   bandwidth, but one launch beats two for partitions of up to about a
-//   million values.
+// One-pass schedule: a single launch; each workgroup streams one tile, ranks it,
+//   finds its output offset by look-back over the tiles before it and places
+//   its pairs itself.  For partitions (and sweeps) of up to kOnePassMax
+//   values, where the staged schedule's second launch and scan tail cost more
+//   than the look-back's contention, and wherever no staging memory exists.
 // accumulate_kernel: the error-feedback addition alone, for the part of the
 //   vector a full pass does not search.
 #include "sparsify_kernel.h"
@@ -71,6 +71,9 @@ constexpr uint64_t kFlagMask = 3ull << 32;
 constexpr int kLookbackDepth = 4;  // chunk status words per lane and chunk look-back round
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+// Four consecutive values at any 4-byte aligned address: gfx950 global loads
+// need dword alignment only, so this is one global_load_dwordx4 too.
+typedef float f32x4_dword __attribute__((ext_vector_type(4), aligned(4)));
 
 __device__ __forceinline__ uint32_t lanes_below(uint64_t mask) {
     return __builtin_amdgcn_mbcnt_hi(static_cast<uint32_t>(mask >> 32),
@@ -142,10 +145,9 @@ __device__ __forceinline__ void store_status(uint64_t* p, uint64_t v) {
 }
 
 // Look-back by all 64 lanes of one wavefront over the status words of the
-// items (tiles or chunks) before `item`: sums their counts back to the nearest
-// inclusive prefix and returns the exclusive prefix (uniform).  Callers draw
-// their items from a ticket counter, so every earlier item belongs to a
-// running workgroup that publishes its count without waiting for later ones:
+// items (groups of tiles) before `item`: sums their counts back to the nearest
+// inclusive prefix and returns the exclusive prefix (uniform).  Every word
+// before `item` is published without waiting for `item` or a later one, so
 // the retries end.
 __device__ uint32_t lookback(const uint64_t* status, uint32_t item, uint32_t epoch, int lane) {
     const uint64_t tag = static_cast<uint64_t>(epoch) << kEpochShift;
@@ -402,15 +404,6 @@ constexpr int kWindowBatch = 8;    // window loads in flight per thread
 // s_waitcnt operand (gfx9 encoding): vector-memory count 0, export and
 // LDS/scalar-memory counts at their maxima (not waited for)
 constexpr int kWaitVmcnt0 = 0x0F70;
-
-// Draws the workgroup's ticket (thread 0) and rearms the counter when the
-// last ticket of the launch is drawn: every other workgroup of the launch has
-// drawn its ticket by then.
-__device__ __forceinline__ uint32_t draw_ticket(unsigned long long* counter, uint32_t last) {
-    const uint32_t drawn = static_cast<uint32_t>(atomicAdd(counter, 1ull));
-    if (drawn == last) __hip_atomic_store(counter, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    return drawn;
-}
 
 // Segment of a sweep holding global tile `tile` (or scan chunk `chunk`): the
 // last segment whose first tile (chunk) is <= it, so empty segments are
@@ -1244,56 +1237,261 @@ __global__ __launch_bounds__(kMoveBlock) void move_sweep_kernel(LaunchArgs a, Sw
 }
 
 // ---------------------------------------------------------------------------
-// Ticket schedule (variant 1)
+// One-pass schedule
 // ---------------------------------------------------------------------------
 
-constexpr int kTicketBlock = 256;
+constexpr int kPassBlock = kPassStream + kWaveSize;  // the streaming threads and the placing wavefront
+constexpr uint32_t kPassCap = 1024;                  // pairs a tile stages in LDS
 
-template <int VEC, int ROWS>
-__global__ __launch_bounds__(kTicketBlock) void ticket_kernel(LaunchArgs a) {
-    constexpr int WAVES = kTicketBlock / kWaveSize;
-    static_assert(VEC * ROWS * kTicketBlock == kTicketTile, "tile size");
-    __shared__ uint32_t s_tile;
-    __shared__ uint32_t s_exclusive;
-    __shared__ uint32_t s_wave_total[ROWS * WAVES];
+// Values of one tile in registers, ROWS rows of one dwordx4 per thread: value
+// (row, thread, c) sits at base + row * kPassRow + thread * 4 + c, which is
+// also its output order.  Addresses are a uniform base plus a 32-bit offset
+// per thread: 64-bit addresses per value took the four-row kernel to 91
+// vector registers, this form needs 58.
+template <int ROWS>
+struct PassTile {
+    int64_t base;      // global index of the tile's first value (uniform)
+    int32_t lo, hi;    // offsets [lo, hi) of the tile's values inside [start, end)
+    float v[ROWS][4];  // acc
+    __device__ __forceinline__ bool interior() const { return lo == 0 && hi == ROWS * kPassRow; }
+    __device__ __forceinline__ bool inside(int32_t j) const { return j >= lo && j < hi; }
+};
 
-    const int tid = threadIdx.x;
-    const int lane = tid & (kWaveSize - 1);
-    const int wave = tid / kWaveSize;
+// Offset inside the tile of thread tid's value c of row r.
+__device__ __forceinline__ int32_t pass_offset(int r, uint32_t tid, int c) {
+    return r * kPassRow + static_cast<int32_t>(tid) * 4 + c;
+}
 
-    if (tid == 0) s_tile = draw_ticket(a.ticket, a.num_tiles - 1);
-    __syncthreads();
-    const uint32_t tile = s_tile;
-    if (tile >= a.num_tiles) return;  // only reachable if the counter was not rearmed
+// Loads the tile and forms acc = grad + residual (one binary32 add): every
+// load of an interior tile is issued before the first value is used, all
+// non-temporal (ResNet-50 rank 0's step 26.6 us of wall time against 28.6 us
+// with temporal ones).  The residual's loads are 16-byte aligned by the choice
+// of a.base, the gradient's 4-byte aligned.  A tile that crosses start or end
+// loads value by value inside [start, end) and holds 0 elsewhere.
+template <int ROWS>
+__device__ __forceinline__ void pass_load(const LaunchArgs& a, PassTile<ROWS>& t, uint32_t tid) {
+    const float* grad = a.grad + t.base;
+    const float* residual = a.residual + t.base;
+    if (t.interior()) {
+        f32x4 g[ROWS], e[ROWS];
+#pragma unroll
+        for (int r = 0; r < ROWS; ++r)
+            g[r] = __builtin_nontemporal_load(reinterpret_cast<const f32x4_dword*>(grad + r * kPassRow) + tid);
+#pragma unroll
+        for (int r = 0; r < ROWS; ++r)
+            e[r] = __builtin_nontemporal_load(reinterpret_cast<const f32x4*>(residual + r * kPassRow) + tid);
+#pragma unroll
+        for (int r = 0; r < ROWS; ++r)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) t.v[r][c] = g[r][c] + e[r][c];
+    } else {
+#pragma unroll
+        for (int r = 0; r < ROWS; ++r)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const int32_t j = pass_offset(r, tid, c);
+                t.v[r][c] = t.inside(j) ? grad[j] + residual[j] : 0.0f;
+            }
+    }
+}
 
-    Tile<VEC, ROWS, kTicketBlock> t;
-    uint32_t lane_rank[ROWS], row_count[ROWS], row_base[ROWS];
-    load_tile<VEC, ROWS, kTicketBlock, false>(a, a.base + static_cast<int64_t>(tile) * kTicketTile, tid, t);
-    const uint32_t sel = compute_tile(a, tid, t);
-    store_residual<VEC, ROWS, kTicketBlock, false>(a, tid, t, sel);
-    wave_ranks<VEC, ROWS>(sel, lane_rank, row_count);
-    const uint32_t count = tile_ranks<ROWS, WAVES>(row_count, lane, wave, s_wave_total, row_base);
-    if (wave == 0) {
-        const uint64_t tag = static_cast<uint64_t>(a.epoch) << kEpochShift;
-        uint32_t excl = 0;
-        if (tile == 0) {
-            if (lane == 0) store_status(&a.status[0], tag | kFlagInclusive | count);
-        } else {
-            if (lane == 0) store_status(&a.status[tile], tag | kFlagAggregate | count);
-            excl = lookback(a.status, tile, a.epoch, lane);
-            if (lane == 0) store_status(&a.status[tile], tag | kFlagInclusive | (excl + count));
+// The thread's selection bits, bit r * 4 + c for value (r, tid, c); values
+// outside [start, end) are never selected.
+template <int ROWS>
+__device__ __forceinline__ uint32_t pass_select(float theta_f, const PassTile<ROWS>& t, uint32_t tid) {
+    static_assert(ROWS * 4 <= 32, "selection bits");
+    uint32_t sel = 0;
+#pragma unroll
+    for (int r = 0; r < ROWS; ++r)
+#pragma unroll
+        for (int c = 0; c < 4; ++c) sel |= static_cast<uint32_t>(__builtin_fabsf(t.v[r][c]) >= theta_f) << (r * 4 + c);
+    if (!t.interior()) {
+#pragma unroll
+        for (int r = 0; r < ROWS; ++r)
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+                if (!t.inside(pass_offset(r, tid, c))) sel &= ~(1u << (r * 4 + c));
+    }
+    return sel;
+}
+
+// residual = selected ? +0 : acc, inside [start, end) only.
+template <int ROWS>
+__device__ __forceinline__ void pass_store(const LaunchArgs& a, const PassTile<ROWS>& t, uint32_t tid, uint32_t sel) {
+    float* residual = a.residual + t.base;
+    if (t.interior()) {
+#pragma unroll
+        for (int r = 0; r < ROWS; ++r) {
+            f32x4 out;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) out[c] = selected<4>(sel, r, c) ? 0.0f : t.v[r][c];
+            __builtin_nontemporal_store(out, reinterpret_cast<f32x4*>(residual + r * kPassRow) + tid);
         }
-        if (lane == 0) {
-            s_exclusive = excl;
-            if (tile == a.num_tiles - 1) {
-                a.count_out[0] = static_cast<int64_t>(excl) + count;
-                a.host_count[0] = static_cast<int64_t>(excl) + count;
-                a.host_count[1] = 0;
+    } else {
+#pragma unroll
+        for (int r = 0; r < ROWS; ++r)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const int32_t j = pass_offset(r, tid, c);
+                if (t.inside(j)) residual[j] = selected<4>(sel, r, c) ? 0.0f : t.v[r][c];
+            }
+    }
+}
+
+// Output offset of tile `tile`, by one wavefront (uniform): the counts of the
+// tiles before it in its group of kGroupTiles, each published by its own
+// workgroup, and the pairs of all groups before, by look-back over group
+// words; the group's last tile publishes the group's word.  Only the words
+// still missing are read again.  Every word waited for belongs to a
+// workgroup of lower index in the same launch, which publishes its tile's
+// count without waiting for anyone, and each XCD dispatches its workgroups in
+// index order, so by induction on the index every wait ends (the argument of
+// the fused launch above).
+//
+// The look-back is bound by how often the same status lines are read: with
+// its offsets made up the kernel runs 2.5 us faster on 3.2M values, and one
+// read of the words costs as much as polling them.  Wall time of a step on
+// 11.7M values with groups of 64, 128, 256 and 512 tiles: 56, 49, 46 and
+// 45.7 us (more, smaller groups put more readers on the few group words);
+// 16-bit words, 64 to a line: 62 us; a chain of group prefixes, each in 16
+// copies, instead of the group look-back: 53 us.
+__device__ __forceinline__ uint32_t pass_offset_of(const LaunchArgs& a, uint32_t tile, uint32_t count, int lane) {
+    constexpr int PER = kGroupTiles / kWaveSize;
+    const uint64_t tag = static_cast<uint64_t>(a.epoch) << kEpochShift;
+    const uint32_t group = tile / kGroupTiles;
+    const uint32_t mine = tile % kGroupTiles;
+    const uint64_t* words = a.status + static_cast<size_t>(group) * kGroupTiles + lane;
+    uint32_t pending = 0, sum = 0;
+#pragma unroll
+    for (int i = 0; i < PER; ++i)
+        if (static_cast<uint32_t>(i * kWaveSize + lane) < mine) pending |= 1u << i;
+    for (;;) {  // uniform
+        uint64_t w[PER];
+#pragma unroll
+        for (int i = 0; i < PER; ++i) w[i] = (pending >> i) & 1u ? load_status(words + i * kWaveSize) : 0ull;
+#pragma unroll
+        for (int i = 0; i < PER; ++i) {
+            if (((pending >> i) & 1u) && (w[i] >> kEpochShift) == a.epoch) {
+                sum += static_cast<uint32_t>(w[i] & kCountMask);
+                pending &= ~(1u << i);
             }
         }
+        if (__ballot(pending != 0) == 0) break;
+        __builtin_amdgcn_s_sleep(4);
     }
-    __syncthreads();
-    scatter_pairs(a, tid, t, sel, s_exclusive, row_base, lane_rank);
+    const uint32_t in_group = wave_sum(sum);
+    const bool publishes = mine == kGroupTiles - 1 && lane == 0;
+    if (publishes)
+        store_status(&a.group_status[group], tag | (group == 0 ? kFlagInclusive : kFlagAggregate) | (in_group + count));
+    if (group == 0) return in_group;
+    const uint32_t before = lookback(a.group_status, group, a.epoch, lane);
+    if (publishes) store_status(&a.group_status[group], tag | kFlagInclusive | (before + in_group + count));
+    return before + in_group;
+}
+
+// One tile per workgroup: four wavefronts stream it, a fifth, which holds no
+// values, publishes the tile's count, looks back and places the pairs.  The
+// streaming wavefronts leave once the pairs are in LDS, so a waiting tile
+// keeps one wavefront slot of five busy, and the look-back's loads do not
+// queue behind the residual stores (gfx9's vmcnt counts stores too).  A tile
+// with more than kPassCap selected values keeps its wavefronts until its
+// offset is known and places its pairs straight from registers.
+//
+// Bound by launch, load and look-back latency.  Wall time of a step before (a
+// kernel whose tiles came from a ticket counter and whose first streaming
+// wavefront looked back, up to 2^20 values; the staged schedule above) and
+// now: 262,144 values 20.9 and 19.3 us, 600,001 23.3 and 20.0, 1,048,577 24.6
+// and 19.9, 3,194,629 29.8 and 27.4.  The allocation-free step: 41.9M values
+// 190 and 118 us, 400M 1.49 and 0.91 ms.
+template <int ROWS>
+__global__ __launch_bounds__(kPassBlock) void one_pass_kernel(LaunchArgs a) {
+    constexpr int WAVES = kPassStream / kWaveSize;
+    constexpr int32_t TILE = ROWS * kPassRow;
+    __shared__ uint32_t s_wave_total[ROWS * WAVES];
+    __shared__ uint2 s_pair[kPassCap];  // (index, value bits)
+    __shared__ uint32_t s_exclusive;
+    const uint32_t tid = threadIdx.x;
+    const int lane = tid & (kWaveSize - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(tid / kWaveSize);
+    const uint32_t tile = blockIdx.x;
+    if (wave < WAVES) {
+        PassTile<ROWS> t;
+        t.base = a.base + static_cast<int64_t>(tile) * TILE;
+        t.lo = t.base < a.start ? static_cast<int32_t>(a.start - t.base) : 0;
+        t.hi = t.base + TILE > a.end ? static_cast<int32_t>(a.end - t.base) : TILE;
+        pass_load<ROWS>(a, t, tid);
+        const uint32_t sel = pass_select<ROWS>(a.theta_f, t, tid);
+        uint32_t lane_rank[ROWS], row_count[ROWS], row_base[ROWS];
+        wave_ranks<4, ROWS>(sel, lane_rank, row_count);
+        const uint32_t count = tile_ranks<ROWS, WAVES>(row_count, lane, wave, s_wave_total, row_base);  // barrier 1
+        // the two placements share no code: what they share would be kept in
+        // registers across the barriers (76 instead of 58 with four rows)
+        if (count <= kPassCap) {  // uniform
+#pragma unroll
+            for (int r = 0; r < ROWS; ++r) {
+                uint32_t pos = row_base[r] + lane_rank[r];
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    if (selected<4>(sel, r, c)) {
+                        s_pair[pos] = make_uint2(static_cast<uint32_t>(t.base) + r * kPassRow + tid * 4 + c,
+                                                 __float_as_uint(t.v[r][c]));
+                        ++pos;
+                    }
+                }
+            }
+            __syncthreads();  // barrier 2
+            pass_store<ROWS>(a, t, tid, sel);
+            return;
+        }
+        __syncthreads();  // barrier 2
+        pass_store<ROWS>(a, t, tid, sel);
+        __syncthreads();  // barrier 3
+#pragma unroll
+        for (int r = 0; r < ROWS; ++r) {
+            uint32_t pos = s_exclusive + row_base[r] + lane_rank[r];
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                if (selected<4>(sel, r, c)) {
+                    a.out_idx[pos] = static_cast<int32_t>(static_cast<uint32_t>(t.base) + r * kPassRow + tid * 4 + c);
+                    a.out_val[pos] = t.v[r][c];
+                    ++pos;
+                }
+            }
+        }
+        return;
+    }
+    __syncthreads();  // barrier 1
+    const uint32_t part = lane < ROWS * WAVES ? s_wave_total[lane] : 0u;
+    const uint32_t count = wave_sum(part);
+    if (lane == 0)
+        store_status(&a.status[tile], (static_cast<uint64_t>(a.epoch) << kEpochShift) | kFlagAggregate | count);
+    __syncthreads();  // barrier 2: the pairs are in LDS
+    const uint32_t excl = pass_offset_of(a, tile, count, lane);
+    if (count > kPassCap) {  // uniform
+        if (lane == 0) s_exclusive = excl;
+        __syncthreads();  // barrier 3
+    } else {
+        for (uint32_t j = lane; j < count; j += kWaveSize) {
+            const uint2 p = s_pair[j];
+            a.out_idx[excl + j] = static_cast<int32_t>(p.x);
+            a.out_val[excl + j] = __uint_as_float(p.y);
+        }
+    }
+    // What goes to mapped host memory, last: a store over the bus ahead of the
+    // look-back's loads would hold them up for its round trip.
+    if (a.host_dense) {  // rows with more selected values than a staging slot holds
+        uint32_t row = part;
+        row += __shfl_xor(row, 1, kWaveSize);
+        row += __shfl_xor(row, 2, kWaveSize);
+        static_assert(WAVES == 4, "a row's four wavefront counts");
+        const uint64_t dense = __ballot(lane % WAVES == 0 && row > kStageCap);
+        if (dense && lane == 0) a.host_dense[tile] = static_cast<uint8_t>(__popcll(dense));
+    }
+    if (tile == a.num_tiles - 1 && lane == 0) {
+        a.count_out[0] = static_cast<int64_t>(excl) + count;
+        a.host_count[0] = static_cast<int64_t>(excl) + count;
+        a.host_count[1] = 0;
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -1439,15 +1637,19 @@ hipError_t launch_sweep(const LaunchArgs& args, const SweepTable& table, bool ve
     return hipGetLastError();
 }
 
-hipError_t launch_ticket(const LaunchArgs& args, bool vec4, hipStream_t stream) {
+hipError_t launch_one_pass(const LaunchArgs& args, int rows, hipStream_t stream) {
     if (!all_set(args.grad, args.residual, args.out_idx, args.out_val, args.count_out, args.host_count, args.status,
-                 args.ticket))
+                 args.group_status))
         return hipErrorInvalidValue;
-    const dim3 grid(args.num_tiles), block(kTicketBlock);
-    if (vec4)
-        hipLaunchKernelGGL((ticket_kernel<4, 4>), grid, block, 0, stream, args);
+    const dim3 grid(args.num_tiles), block(kPassBlock);
+    if (rows == kPassRowsSmall)
+        hipLaunchKernelGGL(one_pass_kernel<kPassRowsSmall>, grid, block, 0, stream, args);
+    else if (rows == kPassRowsMid)
+        hipLaunchKernelGGL(one_pass_kernel<kPassRowsMid>, grid, block, 0, stream, args);
+    else if (rows == kPassRowsLarge)
+        hipLaunchKernelGGL(one_pass_kernel<kPassRowsLarge>, grid, block, 0, stream, args);
     else
-        hipLaunchKernelGGL((ticket_kernel<1, 16>), grid, block, 0, stream, args);
+        return hipErrorInvalidValue;
     return hipGetLastError();
 }
 

@@ -9,20 +9,23 @@
 
 namespace micro {
 
-// The allocation-free step runs the one-pass ticket schedule with its
-// scratch in one static device array per device, of kStaticScratchWords
-// 64-bit words (4 MiB + 256 bytes):
-//   word 0                    the ticket counter (0 between launches)
-//   words 1, 2                count_out: the selected count, the flagged word
-//   words 3, 4                where the kernel stores the counts it would
+// The allocation-free step runs the one-pass schedule with its scratch in one
+// static device array per device, of kStaticScratchWords 64-bit words
+// (4 MiB + 8.5 KB):
+//   words 0, 1                count_out: the selected count, the flagged word
+//   words 2, 3                where the kernel stores the counts it would
 //                             otherwise store into mapped host memory
 //   words kStaticHeaderWords  one look-back status word per tile, for up to
-//   ...                       kStaticMaxTiles 4096-value tiles: a partition of
-//                             up to 2^31 - 1 values (the int32 index range)
-//                             plus the 16-byte alignment of its first tile
+//   ...                       kStaticMaxTiles tiles of 4096 values (or more,
+//                             longer or fewer ones): a partition of up to
+//                             2^31 - 1 values (the int32 index range) plus the
+//                             16-byte alignment of its first tile
+//   the last                  one look-back word per group of tiles
+//   kStaticMaxGroups words
 constexpr int64_t kStaticHeaderWords = 32;  // 256 bytes: the status words stay 256-byte aligned
-constexpr int64_t kStaticMaxTiles = ((int64_t(1) << 31) + 2 + kTicketTile - 1) / kTicketTile;
-constexpr int64_t kStaticScratchWords = kStaticHeaderWords + kStaticMaxTiles;
+constexpr int64_t kStaticMaxTiles = ((int64_t(1) << 31) + 2 + 4095) / 4096;
+constexpr int64_t kStaticMaxGroups = (kStaticMaxTiles + kGroupTiles - 1) / kGroupTiles;
+constexpr int64_t kStaticScratchWords = kStaticHeaderWords + kStaticMaxTiles + kStaticMaxGroups;
 
 // The device address of the static scratch on the current device, looked up
 // once per device with hipGetSymbolAddress and kept.  Thread-safe.

@@ -10,7 +10,7 @@ import torch
 
 import oracle
 import paper_2310_00967_amd as micro
-from paper_2310_00967_amd import synth
+from paper_2310_00967_amd import _lib, synth
 
 from gpu_harness import ParityRun, first_mismatch, note
 
@@ -525,3 +525,60 @@ def test_two_contexts_on_two_streams():
             c["theta"] = th
     for c in cases:
         c["sp"].close()
+
+
+@pytest.mark.parametrize("length", [
+    1, 3, 1023, 1025,                      # one tile of one row, and its edges
+    (1 << 19) - 1, (1 << 19) + 1,          # one row per tile, then four; 512 one-row tiles are one look-back group
+    (1 << 20) + 1,                         # AUTO reports the staged schedule from here on
+    512 * 4096, 512 * 4096 + 1,            # one look-back group of four-row tiles, then two
+    (1 << 22) - 5, 1 << 22, (1 << 22) + 1,  # the last lengths in one launch, the first on the staged kernels
+    (1 << 23) + 4097,                      # six rows per tile (one-pass contexts only)
+])
+@pytest.mark.parametrize("offset", [0, 1, 3])
+def test_one_launch_at_the_edges_of_its_tiles_groups_and_dispatch(length, offset):
+    """The one-launch step under AUTO, TICKET and the allocation-free entry on
+    a vector of `length` values, the residual `offset` values past a 16-byte
+    boundary, with grad and residual at the same and at different 16-byte phases, a dense run whose
+    tiles hold more pairs than they stage, and a NaN, an infinity and a tie at
+    the threshold: the oracle's bits each time."""
+    note(f"one launch length={length} offset={offset}")
+    rng = np.random.default_rng(length + offset)
+    N, world, rank = length, 1, 0
+    g = rng.standard_normal(N).astype(np.float32)
+    g[N // 3:N // 3 + 20_000] *= 30.0
+    if N > 1000:
+        g[N // 2], g[N // 2 + 1], g[N - 1] = np.nan, -np.inf, np.float32(2.5)
+    res0 = (rng.standard_normal(N) * 0.5).astype(np.float32)
+    res0[N - 1] = 0.0
+    o_res = res0.copy()
+    o_idx, o_val, k_or, th_or = oracle.step(g, o_res, rank, world, 0.01, 2.5)
+    for g_off in (offset, (offset + 1) % 4):  # shared phase, then another
+        gbuf = torch.empty(N + 8, dtype=torch.float32, device=DEV)
+        rbuf = torch.full((N + 8,), 7.0, dtype=torch.float32, device=DEV)
+        g_dev, r_dev = gbuf[g_off:g_off + N], rbuf[offset:offset + N]
+        g_dev.copy_(torch.from_numpy(g))
+        for entry in ("auto", "ticket", "noalloc"):
+            r_dev.copy_(torch.from_numpy(res0))
+            oi = torch.full((N + 4,), -9, dtype=torch.int32, device=DEV)
+            ov = torch.full((N + 4,), -9.0, dtype=torch.float32, device=DEV)
+            where = (length, offset, g_off, entry)
+            if entry == "noalloc":
+                k, th = _lib.micro_sparsify_step_noalloc(g_dev.data_ptr(), r_dev.data_ptr(), N, rank, world, 0.01, 2.5,
+                                                         oi.data_ptr(), ov.data_ptr())
+            else:
+                sp = micro.Sparsifier(N, device=DEV,
+                                      variant=TICKET if entry == "ticket" else micro.MICRO_VARIANT_AUTO)
+                k, th, _, _ = sp.step(g_dev, r_dev, rank, world, 0.01, 2.5, oi, ov)
+                _, redone, variant, fused = sp.last_stats()
+                staged = entry == "auto" and N > 1 << 20
+                assert (variant, fused) == ((STAGED, 1) if staged else (TICKET, 0)), where
+                assert (redone > 0) == staged, where
+                sp.close()
+            torch.cuda.synchronize()
+            assert (k, th) == (k_or, th_or), where
+            assert np.array_equal(oi[:k].cpu().numpy(), o_idx), where
+            assert first_mismatch(ov[:k].cpu().numpy(), o_val) < 0, where
+            assert bool((oi[k:] == -9).all()) and bool((ov[k:] == -9.0).all()), where
+            assert first_mismatch(r_dev.cpu().numpy(), o_res) < 0, where
+            assert bool((rbuf[:offset] == 7.0).all()) and bool((rbuf[offset + N:] == 7.0).all()), where
