@@ -93,8 +93,10 @@ typedef enum micro_status {
                              over the keys and a one-workgroup select after
                              each.  With a hint (and k <= P / 8, STAGED or
                              AUTO) the threshold step runs first at 7/8 of it
-                             and the passes run over its output list, which
-                             a trim then cuts to the top k; if that list holds
+                             or closer (up to 63/64, as the last steps' k-th
+                             magnitudes allowed), the select runs over its
+                             output list and a trim cuts that to the top k,
+                             enqueued together; if that list holds
                              fewer than k values, they go back into the
                              residual and the select starts over on the
                              partition's residual.  Without one
@@ -104,7 +106,7 @@ typedef enum micro_status {
                              left and the trim over its list.               */
 #define MICRO_TOPK_ROUTE_FULL 1      /* micro_step_stats.topk_route: three passes over the partition, then the step */
 #define MICRO_TOPK_ROUTE_LIST 2      /* one pass over the partition, the step, two passes over its list */
-#define MICRO_TOPK_ROUTE_HINT_LIST 3 /* the step at the hint's bound, three passes over its list */
+#define MICRO_TOPK_ROUTE_HINT_LIST 3 /* the step at the hint's bound, the select over its list */
 #define MICRO_TOPK_ROUTE_HINT_PICK 4 /* the step at the hint's bound listed fewer than k: one pass over the
                                         residual, then the values from the k-th magnitude's first-digit bin
                                         up extracted and two passes over them (or the passes and a pick
@@ -177,7 +179,8 @@ MICRO_API void micro_config_default(micro_config *cfg);
  * (n_total > INT32_MAX: indices are int32), MICRO_EHIP (no usable device) or
  * MICRO_ENOMEM.  On failure *ctx is set to NULL.  Every context also holds
  * the top-k comparator's 8 KB of radix-select counters and 64 bytes of mapped
- * host memory.
+ * host memory, and one of MICRO_RULE_TOPK another 90 KB and one byte per 128
+ * values of the vector.
  */
 MICRO_API micro_status micro_sparsify_init(micro_ctx **ctx, int64_t n_total,
                                  void *hip_stream, const micro_config *cfg);

@@ -21,6 +21,13 @@
 #include "static_scratch.h"
 #include "topk_kernel.h"
 
+// The top-k comparator's step under a hint looks from (1 - slack) times the
+// hint up.  The slack follows how far the k-th magnitude fell below the hint
+// in the context's last hinted steps, from kTopkSlackMax (where it starts, and
+// where a list that held fewer than k values puts it back) down to
+// kTopkSlackMin; the result never depends on it.
+constexpr double kTopkSlackMax = 0.125, kTopkSlackMin = 1.0 / 64.0;
+
 struct micro_ctx {
     int device = -1;
     int compute_units = 256;                 // of the device, read at init
@@ -56,6 +63,11 @@ struct micro_ctx {
     double* h_sumsq_dev = nullptr;
     // top-k comparator: radix-select counters and state, and its result for the host
     uint32_t* d_topk = nullptr;              // kTopkBins counters (zero between passes), kTopkStateWords
+    // how far below the hint the next hinted step looks (its share of the hint)
+    double topk_slack = kTopkSlackMax;
+    uint32_t* d_hinted = nullptr;            // MICRO_RULE_TOPK: the hinted select's counters, kTopkHintedWords
+    uint64_t* d_hinted_status = nullptr;     // and its look-back words
+    int64_t hinted_chunks = 0;               // list chunks they hold (two words each)
     int64_t* h_topk = nullptr;               // mapped pinned host memory, kTopkHostWords
     int64_t* h_topk_dev = nullptr;
     uint32_t epoch = 0;                      // epoch of the last launch
@@ -185,6 +197,10 @@ micro_status reset_scratch(micro_ctx* ctx) {
     if (e == hipSuccess && ctx->d_topk)
         e = hipMemsetAsync(ctx->d_topk, 0, sizeof(uint32_t) * (micro::kTopkBins + micro::kTopkStateWords),
                            ctx->stream);
+    if (e == hipSuccess && ctx->d_hinted)
+        e = hipMemsetAsync(ctx->d_hinted, 0, sizeof(uint32_t) * micro::kTopkHintedWords, ctx->stream);
+    if (e == hipSuccess && ctx->d_hinted_status)
+        e = hipMemsetAsync(ctx->d_hinted_status, 0, 2 * sizeof(uint64_t) * ctx->hinted_chunks, ctx->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
     if (e != hipSuccess) return hip_fail(ctx, e, "scratch reset");
     ctx->epoch = 0;
@@ -200,7 +216,7 @@ void release(micro_ctx* ctx) {
         if (ev) (void)hipEventDestroy(ev);
     void* device_buffers[] = {ctx->d_tile_counts, ctx->d_tile_excl, ctx->d_flagged_list, ctx->d_split_tile, ctx->d_tile_sumsq, ctx->d_stage,
                               ctx->d_chunk_status, ctx->d_tile_words, ctx->d_status, ctx->d_group_status,
-                              ctx->d_count, ctx->d_topk};
+                              ctx->d_count, ctx->d_topk, ctx->d_hinted, ctx->d_hinted_status};
     for (void* p : device_buffers)
         if (p) (void)hipFree(p);
     if (ctx->h_count) (void)hipHostFree(ctx->h_count);
@@ -317,12 +333,13 @@ float float_from_bits(uint32_t b) {
 
 // How a top-k step runs.  With a usable hint (the incoming theta, normally
 // the k-th magnitude the last step returned) the threshold step runs first,
-// at 7/8 of the hint rounded down to binary32 (kHint); under the staged
+// at 7/8 to 63/64 of the hint rounded down to binary32 (kHint); under the staged
 // schedule it sets the residual to +0 only from the hint itself up (rounded
 // down to binary32), where the k-th magnitude is expected, so the trim has
 // few residual values to change.  When it lists at least k values (and the
-// staging pairs hold them), the three histogram passes run over that list and
-// the trim cuts it to the top k (kHintList); else the list goes back into the
+// staging pairs hold them), the hinted select (or, where that does not apply,
+// three histogram passes) runs over that list and the trim cuts it to the top
+// k (kHintList); else the list goes back into the
 // residual, which then holds acc over the partition, a first pass runs over
 // the residual and either the values from the k-th magnitude's first-digit
 // bin up are extracted into the list for the other passes and the trim, or
@@ -382,11 +399,10 @@ uint32_t topk_blocks(const micro_ctx* ctx, int64_t n, int64_t values_per_thread)
 }
 
 // The incoming theta as a hint for this step's k-th magnitude: the step
-// first runs at kTopkHintScale times it, rounded down to binary32 (*key: its
-// bits).  Taken when theta is positive and finite, the bound a positive
+// first runs at 1 - slack times it, rounded down to binary32 (*key: its
+// bits).  Taken when theta is positive and finite, 7/8 of it a positive
 // binary32, k at most an eighth of the partition, and the staged scratch
 // there for the trim and the pick.
-constexpr double kTopkHintScale = 0.875;
 
 // The largest binary32 at or below x (x >= 0): FLT_MAX above it.
 float f32_at_or_below(double x) {
@@ -396,15 +412,22 @@ float f32_at_or_below(double x) {
     return f;
 }
 
+// Longest list the hinted select takes, in multiples of k (its grid is sized
+// for it; a workgroup past the list's end leaves at once).  Under error
+// feedback the magnitudes up to the k-th fill up evenly: 7/8 of it lists 2.5 to
+// 7 times k values at a density of 0.01 and up to 31 times at 0.001, 63/64 of it
+// less than twice and five times.
+constexpr int64_t kHintedListMax = 16;
+constexpr int64_t kHintedListMin = int64_t(1) << 18;  // taken whatever k is: 64 workgroups
+
 bool topk_hint_key(const micro_ctx* ctx, double theta, int64_t k, int64_t len, uint32_t* key) {
     if (!ctx->has_staged || !ctx->d_stage || !ctx->d_tile_counts || !ctx->d_tile_sumsq) return false;
     if (!(theta > 0.0) || !std::isfinite(theta) || k > len / 8) return false;
     const int64_t chunks = (len + micro::kTopkTrimChunk - 1) / micro::kTopkTrimChunk;
     if (2 * chunks > ctx->tile_capacity) return false;
-    const double b = theta * kTopkHintScale;
-    if (b > static_cast<double>(std::numeric_limits<float>::max())) return false;
-    const float f = f32_at_or_below(b);
-    if (!(f > 0.0f)) return false;
+    const double b = theta * (1.0 - kTopkSlackMax);
+    if (b > static_cast<double>(std::numeric_limits<float>::max()) || !(f32_at_or_below(b) > 0.0f)) return false;
+    const float f = f32_at_or_below(theta * (1.0 - ctx->topk_slack));
     std::memcpy(key, &f, sizeof *key);
     return true;
 }
@@ -763,11 +786,10 @@ micro_status execute_step(micro_ctx* ctx, const float* grad, float* residual, in
         }
     }
     // AUTO contexts run partitions of up to kOnePassMax values in one launch
-    // and the staged schedule above.  Above kAutoTicketMax the top-k
-    // comparator's step at a hint's bound is the staged kernels', and the scan
-    // pass can be asked for on its own.
+    // and the staged schedule above, or above kAutoTicketMax where the scan
+    // pass is asked for on its own.
     const bool separate = (ctx->cfg.flags & MICRO_FLAG_SEPARATE_SCAN) != 0;
-    const int64_t one_launch_max = topk || separate ? kAutoTicketMax : kOnePassMax;
+    const int64_t one_launch_max = separate ? kAutoTicketMax : kOnePassMax;
     const bool staged = ctx->has_staged && !(ctx->has_one_pass && len <= one_launch_max);
     const bool reports_staged = ctx->has_staged && !(ctx->has_one_pass && len <= kAutoTicketMax);
     const int rows = micro::pass_rows_for(len);
@@ -837,7 +859,9 @@ micro_status execute_step(micro_ctx* ctx, const float* grad, float* residual, in
             plan.route = TopkRoute::kHint;
             plan.threshold_key = hint_key;
             plan.zero_key = hint_key;
-            if (staged) {  // the staged kernels leave acc in the residual below theta_zero
+            // the staged kernels and four-row tiles leave acc in the residual
+            // below theta_zero
+            if (staged || rows == micro::kPassRowsMid) {
                 a.theta_zero = f32_at_or_below(*theta);
                 std::memcpy(&plan.zero_key, &a.theta_zero, sizeof plan.zero_key);
             }
@@ -866,7 +890,36 @@ micro_status execute_step(micro_ctx* ctx, const float* grad, float* residual, in
     // The top-k comparator's work after the step: on the hint's route, what
     // the step's count calls for; else the list route's last passes over the
     // step's output list, and the trim to the top k.
+    bool finished = false;  // nothing left to enqueue or to wait for
     if (topk && plan.route == TopkRoute::kHint) {
+        // The hinted select and the trim read the list's length on the
+        // device, so they follow the step without a wait; where they report
+        // that they do not apply, the host goes on from the list's length.
+        // Wall time with a wait here, three passes with a select each, a trim
+        // of four launches and the list always from 7/8 of the hint up, and
+        // now: ResNet-50 rank 0 89.7 and 55.9 us, BERT-large rank 3 223.5 and
+        // 134.6 us.
+        const int64_t want = topk_count(density, len);
+        micro::TopkHinted hs{};
+        hs.count = ctx->d_count;
+        hs.out_idx = out_idx;
+        hs.out_val = out_val;
+        hs.residual = residual;
+        hs.k = static_cast<uint32_t>(want);
+        hs.key_floor = plan.threshold_key;
+        hs.zero_key = plan.zero_key;
+        hs.max_list = std::min(std::max(kHintedListMax * want, kHintedListMin),
+                               ctx->hinted_chunks * micro::kTopkTrimChunk);
+        hs.words = ctx->d_hinted;
+        hs.status = ctx->d_hinted_status;
+        hs.epoch = a.epoch;
+        hs.host = ctx->h_topk_dev;
+        volatile int64_t* h = ctx->h_topk;
+        h[5] = 0;
+        if ((e = micro::launch_topk_hinted(hs, ctx->stream)) != hipSuccess)
+            return hip_fail(ctx, e, "top-k hinted select launch");
+        if (timed && (e = hipEventRecord(ctx->ev[1], ctx->stream)) != hipSuccess)
+            return hip_fail(ctx, e, "hipEventRecord");
         if ((e = hipStreamSynchronize(ctx->stream)) != hipSuccess) return hip_fail(ctx, e, "hipStreamSynchronize");
         const int64_t listed = host_count[0];
         if (listed < 0 || listed > len) {
@@ -875,14 +928,27 @@ micro_status execute_step(micro_ctx* ctx, const float* grad, float* residual, in
             ctx->needs_reset = true;
             return MICRO_EHIP;
         }
-        const micro_status s = topk_after_hint(ctx, &plan, listed, residual, start, len, density, out_idx, out_val);
-        if (s != MICRO_OK) return s;
+        if (h[5] == 1) {
+            plan.route = TopkRoute::kHintList;
+            plan.listed = listed;
+            plan.kept = want;
+            finished = true;
+            // twice the share by which the k-th magnitude fell, or half the
+            // last slack while it did not
+            const double fell = 1.0 - static_cast<double>(float_from_bits(static_cast<uint32_t>(h[0]))) / *theta;
+            ctx->topk_slack = std::min(kTopkSlackMax, std::max({kTopkSlackMin, 2.0 * fell, 0.5 * ctx->topk_slack}));
+        } else {
+            if (listed < want) ctx->topk_slack = kTopkSlackMax;
+            const micro_status s = topk_after_hint(ctx, &plan, listed, residual, start, len, density, out_idx, out_val);
+            if (s != MICRO_OK) return s;
+        }
     } else if (topk && (e = topk_after_step(ctx, plan, out_idx, out_val, residual)) != hipSuccess) {
         return hip_fail(ctx, e, "top-k launch after the step");
     }
-    if (timed && (e = hipEventRecord(ctx->ev[1], ctx->stream)) != hipSuccess)
+    if (timed && !finished && (e = hipEventRecord(ctx->ev[1], ctx->stream)) != hipSuccess)
         return hip_fail(ctx, e, "hipEventRecord");
-    if ((e = hipStreamSynchronize(ctx->stream)) != hipSuccess) return hip_fail(ctx, e, "hipStreamSynchronize");
+    if (!finished && (e = hipStreamSynchronize(ctx->stream)) != hipSuccess)
+        return hip_fail(ctx, e, "hipStreamSynchronize");
     int64_t selected = host_count[0];
     if (selected < 0 || selected > len) {
         set_error(ctx, "device reported %lld selected of %lld", static_cast<long long>(selected),
@@ -1359,6 +1425,13 @@ micro_status micro_sparsify_init(micro_ctx** out, int64_t n_total, void* hip_str
             ok = hipHostMalloc(&ctx->h_dense, kDenseTiles, hipHostMallocMapped | hipHostMallocCoherent) ==
                      hipSuccess &&
                  hipHostGetDevicePointer(reinterpret_cast<void**>(&ctx->h_dense_dev), ctx->h_dense, 0) == hipSuccess;
+    }
+    if (ok && c.rule == MICRO_RULE_TOPK) {
+        // a hinted step's k is at most an eighth of the partition
+        ctx->hinted_chunks =
+            std::max(kHintedListMax * (n_total / 8), kHintedListMin) / micro::kTopkTrimChunk + 1;
+        ok = hipMalloc(&ctx->d_hinted, sizeof(uint32_t) * micro::kTopkHintedWords) == hipSuccess &&
+             hipMalloc(&ctx->d_hinted_status, 2 * sizeof(uint64_t) * ctx->hinted_chunks) == hipSuccess;
     }
     if (!ok) {
         set_error(nullptr, "device or pinned host allocation failed");

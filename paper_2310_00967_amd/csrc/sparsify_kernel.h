@@ -149,7 +149,7 @@ struct LaunchArgs {
     uint64_t* group_status;             // >= ceil(num_tiles / kGroupTiles) look-back words
     uint8_t* host_dense;                // null, or mapped host memory, zero at launch: per tile its rows with
                                         // more than kStageCap selected values, where there are any
-    // staged schedule, theta_zero > theta_f: of the selected values only those
+    // staged schedule and four-row one-pass tiles, theta_zero > theta_f: of the selected values only those
     // with |acc| >= theta_zero have their residual set to +0; the others keep
     // acc there (the top-k comparator's step at a hint's bound)
     float theta_zero;
@@ -184,7 +184,8 @@ hipError_t launch_staged(const LaunchArgs& args, bool vec4, hipStream_t stream);
 // the same launch and each XCD dispatches its workgroups in index order.
 hipError_t launch_fused(const LaunchArgs& args, bool vec4, hipStream_t stream);
 // The one-pass schedule with tiles of `rows` rows (pass_rows_for); a.base from
-// tile_base_for(residual, start, true).
+// tile_base_for(residual, start, true).  theta_zero above theta_f is honoured
+// with kPassRowsMid rows only.
 hipError_t launch_one_pass(const LaunchArgs& args, int rows, hipStream_t stream);
 // The sweep: num_tiles / num_chunks are the totals over the table's segments.
 // fused: the stream and scan passes in one launch of num_tiles + num_chunks

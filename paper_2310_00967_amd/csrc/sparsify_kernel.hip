@@ -1315,16 +1315,16 @@ __device__ __forceinline__ uint32_t pass_select(float theta_f, const PassTile<RO
     return sel;
 }
 
-// residual = selected ? +0 : acc, inside [start, end) only.
+// residual = zero bit ? +0 : acc, inside [start, end) only.
 template <int ROWS>
-__device__ __forceinline__ void pass_store(const LaunchArgs& a, const PassTile<ROWS>& t, uint32_t tid, uint32_t sel) {
+__device__ __forceinline__ void pass_store(const LaunchArgs& a, const PassTile<ROWS>& t, uint32_t tid, uint32_t zero) {
     float* residual = a.residual + t.base;
     if (t.interior()) {
 #pragma unroll
         for (int r = 0; r < ROWS; ++r) {
             f32x4 out;
 #pragma unroll
-            for (int c = 0; c < 4; ++c) out[c] = selected<4>(sel, r, c) ? 0.0f : t.v[r][c];
+            for (int c = 0; c < 4; ++c) out[c] = selected<4>(zero, r, c) ? 0.0f : t.v[r][c];
             __builtin_nontemporal_store(out, reinterpret_cast<f32x4*>(residual + r * kPassRow) + tid);
         }
     } else {
@@ -1333,7 +1333,7 @@ __device__ __forceinline__ void pass_store(const LaunchArgs& a, const PassTile<R
 #pragma unroll
             for (int c = 0; c < 4; ++c) {
                 const int32_t j = pass_offset(r, tid, c);
-                if (t.inside(j)) residual[j] = selected<4>(sel, r, c) ? 0.0f : t.v[r][c];
+                if (t.inside(j)) residual[j] = selected<4>(zero, r, c) ? 0.0f : t.v[r][c];
             }
     }
 }
@@ -1403,7 +1403,8 @@ __device__ __forceinline__ uint32_t pass_offset_of(const LaunchArgs& a, uint32_t
 // now: 262,144 values 20.9 and 19.3 us, 600,001 23.3 and 20.0, 1,048,577 24.6
 // and 19.9, 3,194,629 29.8 and 27.4.  The allocation-free step: 41.9M values
 // 190 and 118 us, 400M 1.49 and 0.91 ms.
-template <int ROWS>
+// HINT: only the residual of values at or above theta_zero becomes +0.
+template <int ROWS, bool HINT>
 __global__ __launch_bounds__(kPassBlock) void one_pass_kernel(LaunchArgs a) {
     constexpr int WAVES = kPassStream / kWaveSize;
     constexpr int32_t TILE = ROWS * kPassRow;
@@ -1421,6 +1422,7 @@ __global__ __launch_bounds__(kPassBlock) void one_pass_kernel(LaunchArgs a) {
         t.hi = t.base + TILE > a.end ? static_cast<int32_t>(a.end - t.base) : TILE;
         pass_load<ROWS>(a, t, tid);
         const uint32_t sel = pass_select<ROWS>(a.theta_f, t, tid);
+        const uint32_t zero = HINT ? pass_select<ROWS>(a.theta_zero, t, tid) : sel;
         uint32_t lane_rank[ROWS], row_count[ROWS], row_base[ROWS];
         wave_ranks<4, ROWS>(sel, lane_rank, row_count);
         const uint32_t count = tile_ranks<ROWS, WAVES>(row_count, lane, wave, s_wave_total, row_base);  // barrier 1
@@ -1440,11 +1442,11 @@ __global__ __launch_bounds__(kPassBlock) void one_pass_kernel(LaunchArgs a) {
                 }
             }
             __syncthreads();  // barrier 2
-            pass_store<ROWS>(a, t, tid, sel);
+            pass_store<ROWS>(a, t, tid, zero);
             return;
         }
         __syncthreads();  // barrier 2
-        pass_store<ROWS>(a, t, tid, sel);
+        pass_store<ROWS>(a, t, tid, zero);
         __syncthreads();  // barrier 3
 #pragma unroll
         for (int r = 0; r < ROWS; ++r) {
@@ -1642,14 +1644,18 @@ hipError_t launch_one_pass(const LaunchArgs& args, int rows, hipStream_t stream)
                  args.group_status))
         return hipErrorInvalidValue;
     const dim3 grid(args.num_tiles), block(kPassBlock);
-    if (rows == kPassRowsSmall)
-        hipLaunchKernelGGL(one_pass_kernel<kPassRowsSmall>, grid, block, 0, stream, args);
-    else if (rows == kPassRowsMid)
-        hipLaunchKernelGGL(one_pass_kernel<kPassRowsMid>, grid, block, 0, stream, args);
-    else if (rows == kPassRowsLarge)
-        hipLaunchKernelGGL(one_pass_kernel<kPassRowsLarge>, grid, block, 0, stream, args);
-    else
+    if (args.theta_zero > args.theta_f) {
+        if (rows != kPassRowsMid) return hipErrorInvalidValue;
+        hipLaunchKernelGGL((one_pass_kernel<kPassRowsMid, true>), grid, block, 0, stream, args);
+    } else if (rows == kPassRowsSmall) {
+        hipLaunchKernelGGL((one_pass_kernel<kPassRowsSmall, false>), grid, block, 0, stream, args);
+    } else if (rows == kPassRowsMid) {
+        hipLaunchKernelGGL((one_pass_kernel<kPassRowsMid, false>), grid, block, 0, stream, args);
+    } else if (rows == kPassRowsLarge) {
+        hipLaunchKernelGGL((one_pass_kernel<kPassRowsLarge, false>), grid, block, 0, stream, args);
+    } else {
         return hipErrorInvalidValue;
+    }
     return hipGetLastError();
 }
 

@@ -99,6 +99,54 @@ hipError_t launch_topk_trim(int32_t* out_idx, float* out_val, float* residual, i
                             uint32_t zero_key, const uint32_t* words, int64_t* host,
                             const TopkTrimScratch* scratch, hipStream_t stream);
 
+// The hinted select: the exact k-th magnitude of the step's output list and
+// the list cut to the top k, without the host knowing how long the list is.
+// Three launches, which all read the list's length from the device:
+//   1 counts the list's keys in kTopkWindowBins bins of 2^kTopkFineBits keys
+//     from key_floor (the step's threshold) up, everything above them in one
+//     more counter;
+//   2 finds the bin of the k-th key and counts its keys one by one, and in
+//     groups of 2^kTopkGroupBits;
+//   3 finds the k-th key in those and compacts the list in place, one
+//     workgroup per kTopkTrimChunk entries, with the trim's rule.
+// Nothing is written to the list or the residual, and status 4 is reported,
+// where the list is shorter than k or longer than max_list, or the k-th key
+// lies above the bins (1.25 to 1.5 times key_floor's magnitude, by its
+// mantissa): the caller then goes on with the list as it is.
+constexpr int kTopkWindowBins = 256;
+constexpr uint32_t kTopkFineBits = 14;  // 2^14 counters are 64 KB of LDS
+constexpr uint32_t kTopkGroupBits = 7;
+constexpr int kTopkFine = 1 << kTopkFineBits;
+constexpr int kTopkGroups = kTopkFine >> kTopkGroupBits;
+constexpr int kTopkGroupStride = 32;    // a group counter to a 128-byte line: many workgroups add to few of them
+// words: kTopkWindowBins + 1 bin counters (zero at launch, cleared by launch
+// 3), the key and the group counters (cleared by launch 1), then the state of
+// launch 2
+constexpr int kTopkHintedBins = 0;
+constexpr int kTopkHintedFine = 512;
+constexpr int kTopkHintedGroups = kTopkHintedFine + kTopkFine;
+constexpr int kTopkHintedState = kTopkHintedGroups + kTopkGroups * kTopkGroupStride;
+constexpr int kTopkHintedWords = kTopkHintedState + 8;
+constexpr int kTopkKeysBlock = 1024;
+static_assert(kTopkWindowBins + 1 <= kTopkHintedFine, "the bins end before the key counters");
+
+struct TopkHinted {
+    const int64_t* count;  // device: the list's length
+    int32_t* out_idx;      // the list, index-ordered
+    float* out_val;
+    float* residual;
+    uint32_t k;            // 1 <= k <= max_list
+    uint32_t key_floor;    // no key of the list is below it
+    uint32_t zero_key;     // as launch_topk_trim's
+    int64_t max_list;      // longest list taken
+    uint32_t* words;       // kTopkHintedWords
+    uint64_t* status;      // 2 * ceil(max_list / kTopkTrimChunk) look-back words, tagged with the epoch
+    uint32_t epoch;
+    int64_t* host;         // kTopkHostWords: [0] k-th key, [1] greater, [2] equal, [3] equal kept, [4] listed,
+                           // [5] status 1, or 4
+};
+hipError_t launch_topk_hinted(const TopkHinted& args, hipStream_t stream);
+
 // Writes the output list [0, n) back into the residual: residual[idx[j]] =
 // val[j] for every idx[j] in [start, end) (the rest is skipped).  After the
 // threshold step the residual then holds acc over the whole partition (the

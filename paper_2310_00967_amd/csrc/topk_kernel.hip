@@ -7,10 +7,13 @@
 
 #include <type_traits>
 
+#include "sparsify_kernel.h"
+
 namespace micro {
 namespace {
 
 using f32x4 = float __attribute__((ext_vector_type(4)));
+using f32x4_dword = float __attribute__((ext_vector_type(4), aligned(4)));  // loads need dword alignment only
 
 constexpr int kWave = 64;
 
@@ -549,6 +552,296 @@ __global__ __launch_bounds__(kTrimBlock) void topk_trim_copy_kernel(const uint2*
     }
 }
 
+// ---------------------------------------------------------------------------
+// The hinted select (topk_kernel.h)
+// ---------------------------------------------------------------------------
+
+enum HintedState : int { kHintedStatus = 0, kHintedBin = 1, kHintedGreater = 2, kHintedRank = 3 };
+
+__device__ __forceinline__ bool hinted_list_ok(const TopkHinted& a, int64_t n) {
+    return n >= static_cast<int64_t>(a.k) && n <= a.max_list;
+}
+
+// Calls f(key) for the keys of list[0, n), two 16-byte groups per thread in
+// flight (the list is 4-byte aligned; dword-aligned 16-byte loads).
+template <class F>
+__device__ __forceinline__ void for_each_key(const float* list, int64_t n, F f) {
+    const int64_t gtid = static_cast<int64_t>(blockIdx.x) * blockDim.x + threadIdx.x;
+    const int64_t stride = static_cast<int64_t>(gridDim.x) * blockDim.x;
+    const f32x4_dword* l4 = reinterpret_cast<const f32x4_dword*>(list);
+    const int64_t groups = n / 4;
+    int64_t q = gtid;
+    for (; q + stride < groups; q += 2 * stride) {
+        const f32x4 v0 = l4[q];
+        const f32x4 v1 = l4[q + stride];
+#pragma unroll
+        for (int c = 0; c < 4; ++c) f(key_of(v0[c]));
+#pragma unroll
+        for (int c = 0; c < 4; ++c) f(key_of(v1[c]));
+    }
+    if (q < groups) {
+        const f32x4 v0 = l4[q];
+#pragma unroll
+        for (int c = 0; c < 4; ++c) f(key_of(v0[c]));
+    }
+    if (gtid < n - groups * 4) f(key_of(list[groups * 4 + gtid]));
+}
+
+// Launch 1.  Each wavefront counts in a copy of its own in LDS; the workgroup
+// adds the nonzero sums to the global counters, so the pass is bound by
+// workgroups times nonzero bins of global atomics and takes few of both
+// (BERT-large rank 3's list 6.4 us, ResNet-50 rank 0's 4.3 us).
+__global__ __launch_bounds__(kTopkHistBlock) void topk_hinted_bins_kernel(TopkHinted a) {
+    constexpr int WAVES = kTopkHistBlock / kWave;
+    constexpr int BINS = kTopkWindowBins + 1;
+    __shared__ uint32_t s_hist[WAVES][BINS];
+    const int tid = threadIdx.x;
+    for (int i = blockIdx.x * kTopkHistBlock + tid; i < kTopkHintedState - kTopkHintedFine;
+         i += gridDim.x * kTopkHistBlock)
+        a.words[kTopkHintedFine + i] = 0u;
+    const int64_t n = a.count[0];
+    if (!hinted_list_ok(a, n)) return;  // uniform
+    for (int b = tid; b < WAVES * BINS; b += kTopkHistBlock) (&s_hist[0][0])[b] = 0u;
+    __syncthreads();
+    uint32_t* mine = s_hist[tid / kWave];
+    for_each_key(a.out_val, n, [&](uint32_t key) {
+        const uint32_t bin = (key - a.key_floor) >> kTopkFineBits;
+        atomicAdd(&mine[bin < kTopkWindowBins ? bin : kTopkWindowBins], 1u);
+    });
+    __syncthreads();
+    for (int b = tid; b < BINS; b += kTopkHistBlock) {
+        uint32_t c = 0;
+#pragma unroll
+        for (int w = 0; w < WAVES; ++w) c += s_hist[w][b];
+        if (c != 0u) atomicAdd(&a.words[kTopkHintedBins + b], c);
+    }
+}
+
+// The entry of counters[0, COUNT * STRIDE), one every STRIDE words, holding
+// the wanted one, counted from the highest entry down: *entry, *above (the sum
+// of the entries above it) and *at (its own).  Every thread of a BLOCK-thread
+// workgroup gets the result; none found (wanted above the sum) leaves *entry
+// at COUNT.
+template <int BLOCK, int COUNT, int STRIDE>
+__device__ __forceinline__ void find_from_top(const uint32_t* counters, uint32_t wanted, uint32_t* s_wave,
+                                              uint32_t* s_found, uint32_t* entry, uint32_t* above, uint32_t* at) {
+    static_assert(COUNT <= BLOCK, "one counter a thread");
+    const int tid = threadIdx.x;
+    const uint32_t c = tid < COUNT ? counters[(COUNT - 1 - tid) * STRIDE] : 0u;
+    if (tid == 0) s_found[0] = COUNT;
+    uint32_t total;
+    const uint32_t before = block_inclusive_sum<BLOCK>(c, s_wave, &total) - c;  // two barriers
+    if (before < wanted && wanted <= before + c) {
+        s_found[0] = COUNT - 1 - tid;
+        s_found[1] = before;
+        s_found[2] = c;
+    }
+    __syncthreads();
+    *entry = s_found[0];
+    *above = s_found[1];
+    *at = s_found[2];
+    __syncthreads();  // s_found is free again
+}
+
+// Launch 2.  Every workgroup finds the k-th key's bin from the same counters
+// and counts that bin's keys (about a hundredth of the list) in LDS, then
+// adds the nonzero counters to those in memory.  (Adding each key straight
+// to memory, 30 us on BERT-large's list: scattered atomics, and the group
+// counters' few lines.)
+__global__ __launch_bounds__(kTopkKeysBlock) void topk_hinted_keys_kernel(TopkHinted a) {
+    __shared__ uint32_t s_fine[kTopkFine];
+    __shared__ uint32_t s_wave[kTopkKeysBlock / kWave];
+    __shared__ uint32_t s_found[3];
+    uint32_t* state = a.words + kTopkHintedState;
+    const int tid = threadIdx.x;
+    const int64_t n = a.count[0];
+    const uint32_t over = a.words[kTopkHintedBins + kTopkWindowBins];
+    const bool ok = hinted_list_ok(a, n) && over < a.k;  // uniform
+    if (!ok) {
+        if (blockIdx.x == 0 && tid == 0) state[kHintedStatus] = 4u;
+        return;
+    }
+    for (int i = tid; i < kTopkFine; i += kTopkKeysBlock) s_fine[i] = 0u;
+    uint32_t bin, above, in_bin;
+    find_from_top<kTopkKeysBlock, kTopkWindowBins, 1>(a.words + kTopkHintedBins, a.k - over, s_wave, s_found, &bin,
+                                                      &above, &in_bin);  // barriers: the counters are zero
+    if (blockIdx.x == 0 && tid == 0) {
+        state[kHintedStatus] = bin < kTopkWindowBins ? 1u : 4u;
+        state[kHintedBin] = bin;
+        state[kHintedGreater] = over + above;
+        state[kHintedRank] = a.k - over - above;
+    }
+    if (bin >= kTopkWindowBins) return;  // uniform; the counters hold n >= k keys, so not reached
+    for_each_key(a.out_val, n, [&](uint32_t key) {
+        const uint32_t off = key - a.key_floor;
+        if ((off >> kTopkFineBits) == bin) atomicAdd(&s_fine[off & (kTopkFine - 1)], 1u);
+    });
+    __syncthreads();
+    for (int i = tid; i < kTopkFine; i += kTopkKeysBlock) {  // uniform trip count
+        const uint32_t c = s_fine[i];
+        if (__ballot(c != 0u) == 0) continue;  // uniform in the wavefront, which lies inside one group
+        if (c != 0u) atomicAdd(&a.words[kTopkHintedFine + i], c);
+        uint32_t sum = c;
+#pragma unroll
+        for (int off = kWave / 2; off > 0; off >>= 1) sum += __shfl_xor(sum, off, kWave);
+        if ((tid & (kWave - 1)) == 0)
+            atomicAdd(&a.words[kTopkHintedGroups + (i >> kTopkGroupBits) * kTopkGroupStride], sum);
+    }
+}
+
+// Exclusive prefix of item `item` by one wavefront (uniform): look-back over
+// status words (count | flag | epoch, the layout of the step's kernels), four
+// words per lane and round.  A word is published without waiting for later
+// items, so the retries end.
+__device__ __forceinline__ uint32_t hinted_lookback(const uint64_t* status, uint32_t item, uint32_t epoch, int lane) {
+    constexpr int D = 4;
+    uint32_t sum = 0;  // this lane's part
+    int64_t top = static_cast<int64_t>(item) - 1;
+    for (;;) {
+        uint64_t w[D];
+        uint32_t valid = 0, incl = 0;
+#pragma unroll
+        for (int j = 0; j < D; ++j) {
+            const int64_t p = top - (lane * D + j);
+            w[j] = p >= 0 ? __hip_atomic_load(&status[p], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
+                          : (static_cast<uint64_t>(epoch) << kEpochShift) | (2ull << 32);
+        }
+#pragma unroll
+        for (int j = 0; j < D; ++j) {
+            const uint32_t flag = static_cast<uint32_t>(w[j] >> 32) & 3u;
+            const bool v = (w[j] >> kEpochShift) == epoch && flag != 0;
+            valid |= static_cast<uint32_t>(v) << j;
+            incl |= static_cast<uint32_t>(v && flag == 2) << j;
+        }
+        const uint64_t inc_lanes = __ballot(incl != 0);
+        const int first = inc_lanes ? __builtin_ctzll(inc_lanes) : kWave;
+        const uint32_t need = lane < first ? (1u << D) - 1u : lane == first ? (2u << __builtin_ctz(incl)) - 1u : 0u;
+        if (__ballot((need & ~valid) != 0) != 0) {
+            __builtin_amdgcn_s_sleep(2);
+            continue;
+        }
+#pragma unroll
+        for (int j = 0; j < D; ++j)
+            if ((need >> j) & 1u) sum += static_cast<uint32_t>(w[j]);
+        if (inc_lanes) break;
+        top -= kWave * D;
+    }
+#pragma unroll
+    for (int off = kWave / 2; off > 0; off >>= 1) sum += __shfl_xor(sum, off, kWave);
+    return sum;
+}
+
+// Launch 3, bound by the scattered residual stores and the look-back (BERT-large
+// rank 3's list 13.4 us, where the four launches of the trim took 25.4 us and
+// the gaps between them).  A chunk's entries are all in registers, index and value, before
+// its counts are published (the wait and the barrier below), and a chunk
+// stores only once the counts of every chunk before it are published, to
+// positions no later than its own entries': so no store reaches an entry that
+// has not been read, and the list is compacted in place.  Waits are for
+// workgroups of lower index in the same launch only, which publish without
+// waiting; each XCD dispatches its workgroups in index order, so they end.
+__global__ __launch_bounds__(kTrimBlock) void topk_hinted_trim_kernel(TopkHinted a) {
+    constexpr int ROWS = kTrimPer * kTrimWaves;
+    static_assert(ROWS == kWave, "one (row, wavefront) count per lane");
+    __shared__ uint32_t s_wave[kTrimWaves], s_found[3];
+    __shared__ uint32_t s_cnt[2][ROWS];  // greater, equal: counts, then exclusive prefixes
+    __shared__ uint32_t s_before[2];
+    const uint32_t* state = a.words + kTopkHintedState;
+    const int tid = threadIdx.x;
+    const int lane = tid & (kWave - 1);
+    const int wave = tid / kWave;
+    const int64_t n = a.count[0];
+    const bool ok = state[kHintedStatus] == 1u;  // uniform
+    if (blockIdx.x == 0) {
+        for (int b = tid; b < kTopkWindowBins + 1; b += kTrimBlock) a.words[kTopkHintedBins + b] = 0u;
+        if (!ok && tid == 0) a.host[5] = 4;
+    }
+    const int64_t base = static_cast<int64_t>(blockIdx.x) * kTopkTrimChunk;
+    if (!ok || base >= n) return;  // uniform
+    float val[kTrimPer];
+    int32_t idx[kTrimPer];
+    load_rows<0>(a.out_val, base, n, 0.0f, val);  // padding: below every key of the list
+    load_rows<0>(a.out_idx, base, n, int32_t(0), idx);
+    const uint32_t bin = state[kHintedBin], rank = state[kHintedRank];
+    uint32_t group, group_above, in_group, fine, fine_above, equal;
+    find_from_top<kTrimBlock, kTopkGroups, kTopkGroupStride>(a.words + kTopkHintedGroups, rank, s_wave, s_found, &group,
+                                                             &group_above, &in_group);
+    group = group < kTopkGroups ? group : kTopkGroups - 1;
+    find_from_top<kTrimBlock, 1 << kTopkGroupBits, 1>(a.words + kTopkHintedFine + (group << kTopkGroupBits),
+                                                      rank - group_above, s_wave, s_found, &fine, &fine_above, &equal);
+    const uint32_t key = a.key_floor + (bin << kTopkFineBits) + (group << kTopkGroupBits) + fine;
+    const uint32_t keep = rank - group_above - fine_above;
+    if (blockIdx.x == 0 && tid == 0) {
+        a.host[0] = key;
+        a.host[1] = state[kHintedGreater] + group_above + fine_above;
+        a.host[2] = equal;
+        a.host[3] = keep;
+        a.host[4] = n;
+        a.host[5] = 1;
+    }
+    const uint64_t lower_lanes = lane ? (~0ull >> (kWave - lane)) : 0ull;
+    uint32_t rank_g[kTrimPer], rank_t[kTrimPer];
+#pragma unroll
+    for (int j = 0; j < kTrimPer; ++j) {
+        const uint32_t kv = key_of(val[j]);
+        const uint64_t mg = __ballot(kv > key);
+        const uint64_t mt = __ballot(kv == key);
+        rank_g[j] = static_cast<uint32_t>(__popcll(mg & lower_lanes));
+        rank_t[j] = static_cast<uint32_t>(__popcll(mt & lower_lanes));
+        if (lane == 0) {
+            s_cnt[0][j * kTrimWaves + wave] = static_cast<uint32_t>(__popcll(mg));
+            s_cnt[1][j * kTrimWaves + wave] = static_cast<uint32_t>(__popcll(mt));
+        }
+    }
+    __builtin_amdgcn_s_waitcnt(0x0F70);  // vector-memory count 0: the chunk's indices have arrived too
+    __syncthreads();
+    if (wave < 2) {  // wavefront 0: the greater entries; 1: the equal ones
+        uint64_t* status = a.status + wave * ((a.max_list + kTopkTrimChunk - 1) / kTopkTrimChunk);
+        const uint64_t tag = static_cast<uint64_t>(a.epoch) << kEpochShift;
+        const uint32_t own = s_cnt[wave][lane];
+        uint32_t v = own;
+#pragma unroll
+        for (int off = 1; off < kWave; off <<= 1) {
+            const uint32_t o = __shfl_up(v, off, kWave);
+            if (lane >= off) v += o;
+        }
+        const uint32_t total = __shfl(v, kWave - 1, kWave);
+        s_cnt[wave][lane] = v - own;
+        uint64_t* word = status + blockIdx.x;
+        if (lane == 0)
+            __hip_atomic_store(word, tag | ((blockIdx.x == 0 ? 2ull : 1ull) << 32) | total, __ATOMIC_RELAXED,
+                               __HIP_MEMORY_SCOPE_AGENT);
+        uint32_t before = 0;
+        if (blockIdx.x != 0) {
+            before = hinted_lookback(status, blockIdx.x, a.epoch, lane);
+            if (lane == 0)
+                __hip_atomic_store(word, tag | (2ull << 32) | (before + total), __ATOMIC_RELAXED,
+                                   __HIP_MEMORY_SCOPE_AGENT);
+        }
+        if (lane == 0) s_before[wave] = before;
+    }
+    __syncthreads();
+    const uint32_t before_g = s_before[0], before_t = s_before[1];
+#pragma unroll
+    for (int j = 0; j < kTrimPer; ++j) {
+        const int64_t p = base + j * kTrimBlock + tid;
+        if (p >= n) continue;
+        const uint32_t kv = key_of(val[j]);
+        const uint32_t g = before_g + s_cnt[0][j * kTrimWaves + wave] + rank_g[j];
+        const uint32_t t = before_t + s_cnt[1][j * kTrimWaves + wave] + rank_t[j];
+        if (kv > key || (kv == key && t < keep)) {
+            if (kv < a.zero_key) a.residual[idx[j]] = 0.0f;
+            const int64_t to = static_cast<int64_t>(g) + (t < keep ? t : keep);
+            if (to != p) {
+                a.out_idx[to] = idx[j];
+                a.out_val[to] = val[j];
+            }
+        } else if (kv >= a.zero_key) {
+            a.residual[idx[j]] = val[j];
+        }
+    }
+}
+
 // Writes the output list back into the residual (one entry a thread, grid
 // stride); indices outside [start, end) are skipped.
 __global__ __launch_bounds__(kTrimBlock) void topk_restore_kernel(const int32_t* out_idx, const float* out_val,
@@ -752,6 +1045,23 @@ hipError_t launch_topk_trim(int32_t* out_idx, float* out_val, float* residual, i
     const uint32_t copy_blocks = nc < 2048u ? nc : 2048u;
     hipLaunchKernelGGL(topk_trim_copy_kernel, dim3(copy_blocks), dim3(kTrimBlock), 0, stream, scratch->temp, kept,
                        out_idx, out_val, words, scratch->partial, nc, host);
+    return hipGetLastError();
+}
+
+hipError_t launch_topk_hinted(const TopkHinted& a, hipStream_t stream) {
+    if (!a.count || !a.out_idx || !a.out_val || !a.residual || !a.words || !a.status || !a.host || a.k < 1 ||
+        a.max_list < static_cast<int64_t>(a.k) || a.key_floor > kTopkKeyMax)
+        return hipErrorInvalidValue;
+    const int64_t chunks = (a.max_list + kTopkTrimChunk - 1) / kTopkTrimChunk;
+    if (chunks > 0x7FFFFFFFll) return hipErrorInvalidValue;
+    // sixteen values a thread of a list of twice k entries, at most 512
+    // workgroups of 256 threads and 256 of 1024 (64 KB of LDS each)
+    const int64_t want = (2ll * a.k + 4095) / 4096;
+    const uint32_t bins_blocks = static_cast<uint32_t>(want < 512 ? want : 512);
+    const uint32_t keys_blocks = static_cast<uint32_t>(want < 1024 ? (want + 3) / 4 : 256);
+    hipLaunchKernelGGL(topk_hinted_bins_kernel, dim3(bins_blocks), dim3(kTopkHistBlock), 0, stream, a);
+    hipLaunchKernelGGL(topk_hinted_keys_kernel, dim3(keys_blocks), dim3(kTopkKeysBlock), 0, stream, a);
+    hipLaunchKernelGGL(topk_hinted_trim_kernel, dim3(static_cast<uint32_t>(chunks)), dim3(kTrimBlock), 0, stream, a);
     return hipGetLastError();
 }
 

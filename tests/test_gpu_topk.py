@@ -521,3 +521,40 @@ def test_build_up_of_the_comparators_and_its_absence_under_micro():
         assert abs(b["worker_density"]["topk"][t] - k_frac) < 1e-12
         assert k_frac < b["union_density"]["topk"][t] <= n * k_frac + 1e-12
         assert b["union_density"]["hard_threshold"][t] <= n * b["worker_density"]["hard_threshold"][t] + 1e-12
+
+
+@pytest.mark.parametrize("variant", [AUTO, STAGED], ids=["auto", "staged"])
+@pytest.mark.parametrize("listed,k_rank", [
+    (0, 0), (1, 0),              # the list holds exactly k values, and one more
+    (4095, 0), (4096, 0), (4097, 0),  # k and a chunk boundary of the trim
+    (20_000, 1),                 # the k-th magnitude tied across chunks, some of the ties dropped
+    (20_000, 2),                 # the k-th magnitude above the counted keys: the passes take over
+    (270_000, 0),                # a list longer than the hinted select takes
+])
+def test_hinted_select_at_its_limits(variant, listed, k_rank):
+    """A partition whose list under a hint of 1 holds k + `listed` values: at
+    the edges of the hinted select (fewest values, whole chunks, ties cut
+    between chunks, the counted keys' end, the longest list), the one-launch
+    and the staged step; two calls in a row, so the counters are clear again."""
+    N, k = 2_400_000, 2_400
+    rng = np.random.default_rng(listed * 3 + k_rank)
+    g = np.zeros(N, np.float32)
+    at = rng.permutation(N)
+    top = rng.uniform(1.0, 1.05, k).astype(np.float32)
+    if k_rank == 1:
+        top[:] = np.float32(1.03)       # k + listed / 2 equal magnitudes
+    elif k_rank == 2:
+        top[:] = rng.uniform(3.0, 4.0, k).astype(np.float32)
+    rest = rng.uniform(0.9, 0.99, listed).astype(np.float32)
+    if k_rank == 1:
+        rest[: listed // 2] = np.float32(1.03)
+    vals = np.concatenate([top, rest]) * rng.choice(np.float32([-1.0, 1.0]), k + listed)
+    g[at[: k + listed]] = vals
+    g[at[k + listed:]] = rng.uniform(0.0, 0.5, N - k - listed).astype(np.float32)
+    res = np.zeros(N, np.float32)
+    note(f"hinted select limits listed={listed} k_rank={k_rank} variant={variant}")
+    sp = make(N, variant)
+    for _ in range(2):
+        topk_vs_oracle(g, res, 0, 1, 0.001, variant, sp=sp, hint=1.0)
+        assert sp.last_topk_route() == micro.MICRO_TOPK_ROUTE_HINT_LIST
+    sp.close()
