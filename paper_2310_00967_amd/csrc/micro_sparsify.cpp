@@ -1004,6 +1004,11 @@ micro_status run_segments(micro_ctx* ctx, const float* grad, float* residual, in
     table.seg[count].tile_first = static_cast<uint32_t>(tiles);
     table.seg[count].chunk_first = static_cast<uint32_t>(chunks);
     table.seg[count].wg_first = static_cast<uint32_t>(tiles + chunks);
+    while (((tiles + chunks) >> table.bucket_shift) >= micro::kSweepBuckets) ++table.bucket_shift;
+    for (uint32_t i = 0, r = 0; i < micro::kSweepBuckets; ++i) {
+        while (r + 1 < table.count && table.seg[r + 1].wg_first <= static_cast<uint64_t>(i) << table.bucket_shift) ++r;
+        table.bucket[i] = r;
+    }
     if (tiles > ctx->tile_capacity || chunks > ctx->chunk_capacity) {
         set_error(ctx, "sweep needs %lld tiles, scratch holds %lld", static_cast<long long>(tiles),
                   static_cast<long long>(ctx->tile_capacity));

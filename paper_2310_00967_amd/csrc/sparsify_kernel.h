@@ -109,9 +109,12 @@ struct SweepSegment {
                             // out by fused_role); seg[count].wg_first = the launch's workgroups
 };
 
+constexpr uint32_t kSweepBuckets = 64;
+
 struct SweepTable {
     uint32_t count;                       // segments
-    uint32_t pad;
+    uint32_t bucket_shift;                // the launch's workgroups, shifted, lie below kSweepBuckets
+    uint32_t bucket[kSweepBuckets];       // fused sweep: segment of workgroup i << bucket_shift
     SweepSegment seg[kMaxSweep + 1];      // seg[count]: tile_first / chunk_first = the totals
 };
 

@@ -432,14 +432,36 @@ __device__ __forceinline__ uint32_t segment_of_chunk(const SweepTable* tbl, uint
     return lo;
 }
 
-// A sweep segment's range and threshold in the fields the tile helpers read;
-// returns the global index of the first value of the segment's tile `tile`.
-__device__ __forceinline__ int64_t enter_segment(LaunchArgs& a, const SweepTable* tbl, uint32_t tile) {
-    const SweepSegment& sg = tbl->seg[segment_of_tile(tbl, tile)];
+// Segment r's range and threshold in the fields the tile helpers read; returns
+// the global index of the first value of its tile `tile`.
+__device__ __forceinline__ int64_t enter_segment(LaunchArgs& a, const SweepTable* tbl, uint32_t r, uint32_t tile) {
+    const SweepSegment& sg = tbl->seg[r];
     a.start = sg.start;
     a.end = sg.end;
     a.theta_f = sg.theta_f;
     return sg.base + static_cast<int64_t>(tile - sg.tile_first) * kStreamTile;
+}
+
+// Sum of one binary64 value per lane, in a fixed order (the scan of
+// wave_inclusive_sum on both halves of the value); valid in the last lane.
+// (Six data-parallel-primitive steps instead of the twelve LDS-routed
+// permutes of a butterfly.)
+template <int CTRL, int ROW_MASK>
+__device__ __forceinline__ double dpp_add(double x) {
+    const uint64_t b = static_cast<uint64_t>(__double_as_longlong(x));
+    const uint32_t lo = __builtin_amdgcn_update_dpp(0u, static_cast<uint32_t>(b), CTRL, ROW_MASK, 0xf, false);
+    const uint32_t hi = __builtin_amdgcn_update_dpp(0u, static_cast<uint32_t>(b >> 32), CTRL, ROW_MASK, 0xf, false);
+    return x + __longlong_as_double(static_cast<int64_t>((static_cast<uint64_t>(hi) << 32) | lo));
+}
+
+__device__ __forceinline__ double wave_sum_last(double x) {
+    x = dpp_add<kDppRowShr1, 0xf>(x);
+    x = dpp_add<kDppRowShr2, 0xf>(x);
+    x = dpp_add<kDppRowShr4, 0xf>(x);
+    x = dpp_add<kDppRowShr8, 0xf>(x);
+    x = dpp_add<kDppRowBcast15, 0xa>(x);
+    x = dpp_add<kDppRowBcast31, 0xc>(x);
+    return x;
 }
 
 // Sum over the workgroup of one binary64 value per thread, in a fixed order
@@ -475,7 +497,7 @@ __device__ __forceinline__ void publish_tile(const LaunchArgs& a, uint32_t tile,
 // norm of its new residual (also for a tile left to the move kernel, whose
 // new residual is fixed by its selection bits all the same).
 template <int VEC, int ROWS, bool SWEEP, bool FUSED = false, bool HINT = false>
-__device__ __forceinline__ void stream_tile(LaunchArgs a, const SweepTable* tbl, uint32_t tile) {
+__device__ __forceinline__ void stream_tile(LaunchArgs a, const SweepTable* tbl, uint32_t segment, uint32_t tile) {
     constexpr int WAVES = kStreamBlock / kWaveSize;
     static_assert(VEC * ROWS * kStreamBlock == kStreamTile, "tile size");
     __shared__ uint32_t s_wave_total[ROWS * WAVES];
@@ -485,7 +507,7 @@ __device__ __forceinline__ void stream_tile(LaunchArgs a, const SweepTable* tbl,
     const int tid = threadIdx.x;
     const int lane = tid & (kWaveSize - 1);
     const int wave = tid / kWaveSize;
-    const int64_t tile_base = SWEEP ? enter_segment(a, tbl, tile) : a.base + static_cast<int64_t>(tile) * kStreamTile;
+    const int64_t tile_base = SWEEP ? enter_segment(a, tbl, segment, tile) : a.base + static_cast<int64_t>(tile) * kStreamTile;
 
     Tile<VEC, ROWS, kStreamBlock> t;
     uint32_t lane_rank[ROWS], row_count[ROWS], row_base[ROWS];
@@ -502,11 +524,19 @@ __device__ __forceinline__ void stream_tile(LaunchArgs a, const SweepTable* tbl,
                 const double v = selected<VEC>(sel, r, c) ? 0.0 : static_cast<double>(t.v[r][c]);
                 if (i >= a.start && i < a.end) sq += v * v;
             }
-        const double total = block_sum<WAVES>(sq, lane, wave, s_sq);
-        if (tid == 0) a.tile_sumsq[tile] = total;
+        sq = wave_sum_last(sq);
+        if (lane == kWaveSize - 1) s_sq[wave] = sq;
     }
     wave_ranks<VEC, ROWS>(sel, lane_rank, row_count);
-    const uint32_t count = tile_ranks<ROWS, WAVES>(row_count, lane, wave, s_wave_total, row_base);
+    const uint32_t count = tile_ranks<ROWS, WAVES>(row_count, lane, wave, s_wave_total, row_base);  // and s_sq
+    if constexpr (SWEEP) {
+        if (tid == 0) {
+            double total = 0.0;
+#pragma unroll
+            for (int w = 0; w < WAVES; ++w) total += s_sq[w];
+            a.tile_sumsq[tile] = total;
+        }
+    }
     if (count > kStageCap) {  // uniform: left to the move kernel, residual untouched
         if (tid == 0) publish_tile<FUSED>(a, tile, count | kOverflow);
         return;
@@ -535,19 +565,19 @@ __device__ __forceinline__ void stream_tile(LaunchArgs a, const SweepTable* tbl,
 
 template <int VEC, int ROWS>
 __global__ __launch_bounds__(kStreamBlock) void stream_kernel(LaunchArgs a) {
-    stream_tile<VEC, ROWS, false>(a, nullptr, blockIdx.x);
+    stream_tile<VEC, ROWS, false>(a, nullptr, 0, blockIdx.x);
 }
 
 // The stream pass that sets only the residual of values at or above
 // theta_zero to +0.
 template <int VEC, int ROWS>
 __global__ __launch_bounds__(kStreamBlock) void stream_hint_kernel(LaunchArgs a) {
-    stream_tile<VEC, ROWS, false, false, true>(a, nullptr, blockIdx.x);
+    stream_tile<VEC, ROWS, false, false, true>(a, nullptr, 0, blockIdx.x);
 }
 
 template <int VEC, int ROWS>
 __global__ __launch_bounds__(kStreamBlock) void stream_sweep_kernel(LaunchArgs a, SweepTable tbl) {
-    stream_tile<VEC, ROWS, true>(a, &tbl, blockIdx.x);
+    stream_tile<VEC, ROWS, true>(a, &tbl, segment_of_tile(&tbl, blockIdx.x), blockIdx.x);
 }
 
 // Full processing of one flagged tile by one wavefront with its pairs from
@@ -929,7 +959,7 @@ __global__ __launch_bounds__(kStreamBlock) void stream_scan_kernel(LaunchArgs a)
     if (role.scan)
         scan_chunk<false, true>(a, nullptr, role.item);
     else
-        stream_tile<VEC, ROWS, false, true>(a, nullptr, role.item);
+        stream_tile<VEC, ROWS, false, true>(a, nullptr, 0, role.item);
 }
 
 // The fused launch whose stream pass sets only the residual of values at or
@@ -941,7 +971,7 @@ __global__ __launch_bounds__(kStreamBlock) void stream_scan_hint_kernel(LaunchAr
     if (role.scan)
         scan_chunk<false, true>(a, nullptr, role.item);
     else
-        stream_tile<VEC, ROWS, false, true, true>(a, nullptr, role.item);
+        stream_tile<VEC, ROWS, false, true, true>(a, nullptr, 0, role.item);
 }
 
 __global__ __launch_bounds__(kScanBlock) void scan_sweep_kernel(LaunchArgs a, SweepTable tbl) {
@@ -949,18 +979,17 @@ __global__ __launch_bounds__(kScanBlock) void scan_sweep_kernel(LaunchArgs a, Sw
 }
 
 // Segment of a fused sweep holding workgroup b: the last segment whose first
-// workgroup is <= b, so empty segments are skipped.  Uniform binary search
-// over the table in the kernel arguments.
+// workgroup is <= b, so empty segments are skipped.  The table in the kernel
+// arguments gives the segment of the first workgroup of every
+// 2^bucket_shift; the walk from there takes a step or two in a sweep of equal
+// partitions.  Every step is a dependent scalar load at the start of every
+// workgroup, and the launch is bound by how long its workgroups live (a binary
+// search here and another in the tile, with the norm's butterfly and barrier
+// of its own: ResNet-18's sweep launch 31.3 us, now 29.9).
 __device__ __forceinline__ uint32_t segment_of_workgroup(const SweepTable* tbl, uint32_t b) {
-    uint32_t lo = 0, hi = tbl->count;
-    while (hi - lo > 1) {
-        const uint32_t mid = (lo + hi) / 2;
-        if (tbl->seg[mid].wg_first <= b)
-            lo = mid;
-        else
-            hi = mid;
-    }
-    return lo;
+    uint32_t r = tbl->bucket[b >> tbl->bucket_shift];
+    while (r + 1 < tbl->count && tbl->seg[r + 1].wg_first <= b) ++r;
+    return r;
 }
 
 // Fused sweep: the stream and scan passes of every segment in one launch.
@@ -979,7 +1008,7 @@ __global__ __launch_bounds__(kStreamBlock) void stream_scan_sweep_kernel(LaunchA
     if (role.scan)
         scan_chunk<true, true>(a, &tbl, sg.chunk_first + role.item);
     else
-        stream_tile<VEC, ROWS, true, true>(a, &tbl, sg.tile_first + role.item);
+        stream_tile<VEC, ROWS, true, true>(a, &tbl, r, sg.tile_first + role.item);
 }
 
 // Number of output pairs before item x of the merged sequence, given the tile
@@ -1049,7 +1078,7 @@ __device__ __forceinline__ void move_work(const LaunchArgs& a, const SweepTable*
         const uint32_t out_base = a.tile_excl[tile] & ~kOverflow;
         if constexpr (SWEEP) {
             LaunchArgs seg_args = a;
-            const int64_t tile_base = enter_segment(seg_args, tbl, tile);
+            const int64_t tile_base = enter_segment(seg_args, tbl, segment_of_tile(tbl, tile), tile);
             redo_tile<VEC>(seg_args, tile_base, lane, out_base);
         } else {
             redo_tile<VEC, HINT>(a, a.base + static_cast<int64_t>(tile) * kStreamTile, lane, out_base);
