@@ -80,9 +80,14 @@ class Sparsifier:
         self._cycle_p = ctypes.pointer(self._cycle_c)
         self._sumsq_c = ctypes.c_double()
         self._sumsq_p = ctypes.pointer(self._sumsq_c)
+        # the native marshalling of the plain case of step, ef_step and sweep
+        self._caller = _lib.load_caller()(*(ctypes.cast(fn, ctypes.c_void_p).value
+                                            for fn in (self._step_fn, self._ef_fn, self._sweep_fn)),
+                                          self._ctx.value, self.n_total, self.device.index)
 
     def close(self):
         if getattr(self, "_ctx", None) is not None:
+            self._caller = None
             _lib.micro_sparsify_free(self._ctx)
             self._ctx = None
 
@@ -131,9 +136,14 @@ class Sparsifier:
         while the next one runs."""
         if self._ctx is None:
             raise RuntimeError("Sparsifier is closed")
-        length = self._length(rank, world)
         if out_idx is None or out_val is None:
-            out_idx, out_val = self.outputs(length)
+            out_idx, out_val = self.outputs(self._length(rank, world))
+        done = self._caller.step(grad, residual, rank, world, density, theta, out_idx, out_val)
+        if done.__class__ is tuple:
+            return done
+        if done is not None:
+            _lib.check(done, self._ctx)
+        length = self._length(rank, world)
         self._check_vectors(grad, residual, out_idx, out_val)
         if out_idx.numel() < length or out_val.numel() < length:
             raise ValueError(f"output capacity below the partition length {length}")
@@ -167,9 +177,14 @@ class Sparsifier:
         output buffers, as in step."""
         if self._ctx is None:
             raise RuntimeError("Sparsifier is closed")
-        length = self._length(_lib.micro_cycle(t, worker, world), world)
         if out_idx is None or out_val is None:
-            out_idx, out_val = self.outputs(length)
+            out_idx, out_val = self.outputs(self._length(_lib.micro_cycle(t, worker, world), world))
+        done = self._caller.ef_step(grad, residual, t, worker, world, density, theta, out_idx, out_val, local_error)
+        if done.__class__ is tuple:
+            return done
+        if done is not None:
+            _lib.check(done, self._ctx)
+        length = self._length(_lib.micro_cycle(t, worker, world), world)
         self._check_vectors(grad, residual, out_idx, out_val)
         if out_idx.numel() < length or out_val.numel() < length:
             raise ValueError(f"output capacity below the partition length {length}")
@@ -196,6 +211,11 @@ class Sparsifier:
             raise ValueError("one threshold per partition")
         if out_idx is None or out_val is None:
             out_idx, out_val = self.outputs(self.n_total)
+        done = self._caller.sweep(grad, residual, world, density, thetas, out_idx, out_val, want_sumsq)
+        if done.__class__ is tuple:
+            return done
+        if done is not None:
+            _lib.check(done, self._ctx)
         self._check_vectors(grad, residual, out_idx, out_val)
         if out_idx.numel() < self.n_total or out_val.numel() < self.n_total:
             raise ValueError(f"output capacity below n_total {self.n_total}")

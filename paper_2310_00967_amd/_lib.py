@@ -94,6 +94,17 @@ def load():
     return _lib
 
 
+def load_caller():
+    """The native marshalling's Caller type (never builds it)."""
+    import torch  # noqa: F401  (its libraries before the module that links to them)
+    try:
+        from ._caller import Caller
+    except ImportError as e:
+        raise RuntimeError(f"the binding's native part is not built or not loadable ({e}); run "
+                           "__graft_entry__.build() or python -m paper_2310_00967_amd.build") from e
+    return Caller
+
+
 def status_string(status):
     return load().micro_status_string(int(status)).decode()
 
@@ -160,11 +171,9 @@ def micro_sparsify_step_noalloc(grad_ptr, residual_ptr, n_total, rank, world, de
     current device; returns (k, theta_next)."""
     th = ctypes.c_double(float(theta))
     k = ctypes.c_int64()
-    st = load().micro_sparsify_step_noalloc(ctypes.c_void_p(grad_ptr), ctypes.c_void_p(residual_ptr),
-                                            int(n_total), int(rank), int(world), float(density),
-                                            ctypes.byref(th), ctypes.c_void_p(out_idx_ptr),
-                                            ctypes.c_void_p(out_val_ptr), ctypes.byref(k),
-                                            ctypes.c_void_p(stream_handle or 0),
+    st = load().micro_sparsify_step_noalloc(grad_ptr, residual_ptr, int(n_total), int(rank), int(world),
+                                            float(density), ctypes.byref(th), out_idx_ptr, out_val_ptr,
+                                            ctypes.byref(k), stream_handle or None,
                                             ctypes.byref(cfg) if cfg is not None else None)
     check(st)
     return k.value, th.value

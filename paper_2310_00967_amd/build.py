@@ -2,7 +2,9 @@
 
 hipcc compiles the kernel (device + host stub) and the host library
 separately, then links one shared object whose exported symbols are exactly
-the C ABI of include/micro_sparsify.h.  Floating point: no contraction
+the C ABI of include/micro_sparsify.h; g++ compiles the Python binding's
+marshalling against the installed torch's headers (_caller.so, the same C ABI
+reached through the addresses it is given).  Floating point: no contraction
 (-ffp-contract=off), no fast-math, subnormals kept, correctly rounded binary32
 division, and the packed-fp32 instructions disabled for device code.
 """
@@ -17,6 +19,7 @@ CSRC = os.path.join(PKG, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 BUILD_DIR = os.path.join(ROOT, "_build")
 LIB = os.path.join(PKG, "libmicro_sparsify.so")
+CALLER = os.path.join(PKG, "_caller.so")
 ARCH = "gfx950"
 
 
@@ -59,5 +62,24 @@ def build_library(verbose=False, extra_device_flags=()):
     return LIB
 
 
+def build_caller(verbose=False):
+    """Compiles the Python binding's marshalling (every call) and returns its path."""
+    import sysconfig
+
+    import torch
+    from torch.utils.cpp_extension import include_paths
+    tmp = CALLER + ".tmp"
+    libdir = os.path.join(os.path.dirname(torch.__file__), "lib")
+    includes = [sysconfig.get_paths()["include"], *include_paths()]
+    _run([os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-Wall",
+          f"-I{INCLUDE}", *[f"-isystem{d}" for d in includes],
+          f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+          os.path.join(CSRC, "py_caller.cpp"), "-o", tmp, f"-L{libdir}", "-ltorch_python", "-ltorch", "-ltorch_cpu",
+          "-lc10"], verbose)
+    os.replace(tmp, CALLER)
+    return CALLER
+
+
 if __name__ == "__main__":
     print(build_library(verbose=True or "-v" in sys.argv))
+    print(build_caller(verbose=True))

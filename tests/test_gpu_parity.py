@@ -582,3 +582,50 @@ def test_one_launch_at_the_edges_of_its_tiles_groups_and_dispatch(length, offset
             assert bool((oi[k:] == -9).all()) and bool((ov[k:] == -9.0).all()), where
             assert first_mismatch(r_dev.cpu().numpy(), o_res) < 0, where
             assert bool((rbuf[:offset] == 7.0).all()) and bool((rbuf[offset + N:] == 7.0).all()), where
+
+
+def test_native_and_python_marshalling_agree():
+    """The binding's native marshalling takes the plain case and leaves the
+    rest to the Python methods: the same results either way (an integer of
+    another type sends a call to Python), views of the given buffers, and the
+    Python methods' errors."""
+    N, world = 50_001, 3
+    rng = np.random.default_rng(5)
+    g = torch.from_numpy(rng.standard_normal(N).astype(np.float32)).to(DEV)
+    res0 = torch.from_numpy(rng.standard_normal(N).astype(np.float32)).to(DEV)
+    oi = torch.empty(N, dtype=torch.int32, device=DEV)
+    ov = torch.empty(N, dtype=torch.float32, device=DEV)
+    sp = micro.Sparsifier(N, device=DEV)
+    calls = {
+        "step": lambda w, r: sp.step(g, r, 1, w, 0.01, 2.4, oi, ov),
+        "ef": lambda w, r: sp.ef_step(g, r, 7, 1, w, 0.01, 2.4, oi, ov),
+        "ef error": lambda w, r: sp.ef_step(g, r, 7, 1, w, 0.01, 2.4, oi, ov, local_error=True),
+        "sweep": lambda w, r: sp.sweep(g, r, w, 0.01, [2.2, 2.4, 2.6], oi, ov),
+        "sweep, no norms": lambda w, r: sp.sweep(g, r, w, 0.01, [2.2, 2.4, 2.6], oi, ov, want_sumsq=False),
+    }
+    for name, call in calls.items():
+        got = []
+        for w in (world, np.int64(world)):
+            r = res0.clone()
+            out = call(w, r)
+            views = [x for x in out if isinstance(x, torch.Tensor)]
+            assert [v.data_ptr() for v in views] == [oi.data_ptr(), ov.data_ptr()], name
+            got.append([x for x in out if not isinstance(x, torch.Tensor)] + [v.cpu().numpy().tobytes() for v in views]
+                       + [r.cpu().numpy().tobytes()])
+        assert got[0] == got[1], name
+    r = res0.clone()
+    for bad, error in [(lambda: sp.step(g.double(), r, 0, world, 0.01, 2.4), TypeError),
+                       (lambda: sp.step(g, r[:-1], 0, world, 0.01, 2.4), ValueError),
+                       (lambda: sp.step(g, r, 0, world, 0.01, 2.4, oi[:10], ov), ValueError),
+                       (lambda: sp.step(g, r.cpu(), 0, world, 0.01, 2.4, oi, ov), TypeError),
+                       (lambda: sp.step(g, r, world, world, 0.01, 2.4, oi, ov), micro.MicroError),
+                       (lambda: sp.step(g, r, 0, world, 0.01, -1.0, oi, ov), micro.MicroError),
+                       (lambda: sp.step(g, g, 0, world, 0.01, 2.4, oi, ov), micro.MicroError),
+                       (lambda: sp.ef_step(g, r, -1, 0, world, 0.01, 2.4, oi, ov), micro.MicroError),
+                       (lambda: sp.sweep(g, r, world, 0.01, [1.0], oi, ov), ValueError)]:
+        with pytest.raises(error):
+            bad()
+    assert torch.equal(r, res0)
+    sp.close()
+    with pytest.raises(RuntimeError):
+        sp.step(g, r, 0, world, 0.01, 2.4, oi, ov)
