@@ -93,7 +93,7 @@ typedef enum micro_status {
                              over the keys and a one-workgroup select after
                              each.  With a hint (and k <= P / 8, STAGED or
                              AUTO) the threshold step runs first at 7/8 of it
-                             or closer (up to 63/64, as the last steps' k-th
+                             or closer (up to 511/512, as the last steps' k-th
                              magnitudes allowed), the select runs over its
                              output list and a trim cuts that to the top k,
                              enqueued together; if that list holds

@@ -22,11 +22,11 @@
 #include "topk_kernel.h"
 
 // The top-k comparator's step under a hint looks from (1 - slack) times the
-// hint up.  The slack follows how far the k-th magnitude fell below the hint
-// in the context's last hinted steps, from kTopkSlackMax (where it starts, and
+// hint up.  The slack follows how far the k-th magnitude was from the hint in
+// the context's last hinted steps, from kTopkSlackMax (where it starts, and
 // where a list that held fewer than k values puts it back) down to
 // kTopkSlackMin; the result never depends on it.
-constexpr double kTopkSlackMax = 0.125, kTopkSlackMin = 1.0 / 64.0;
+constexpr double kTopkSlackMax = 0.125, kTopkSlackMin = 1.0 / 512.0;
 
 struct micro_ctx {
     int device = -1;
@@ -333,7 +333,7 @@ float float_from_bits(uint32_t b) {
 
 // How a top-k step runs.  With a usable hint (the incoming theta, normally
 // the k-th magnitude the last step returned) the threshold step runs first,
-// at 7/8 to 63/64 of the hint rounded down to binary32 (kHint); under the staged
+// at 7/8 to 511/512 of the hint rounded down to binary32 (kHint); under the staged
 // schedule it sets the residual to +0 only from the hint itself up (rounded
 // down to binary32), where the k-th magnitude is expected, so the trim has
 // few residual values to change.  When it lists at least k values (and the
@@ -414,11 +414,15 @@ float f32_at_or_below(double x) {
 
 // Longest list the hinted select takes, in multiples of k (its grid is sized
 // for it; a workgroup past the list's end leaves at once).  Under error
-// feedback the magnitudes up to the k-th fill up evenly: 7/8 of it lists 2.5 to
-// 7 times k values at a density of 0.01 and up to 31 times at 0.001, 63/64 of it
-// less than twice and five times.
+// feedback the magnitudes up to the k-th fill up: 7/8 of it lists 2.5 to 10
+// times k values at a density of 0.01 and 30 to 50 times at 0.001, 63/64 of it
+// twice and four to seven times.
 constexpr int64_t kHintedListMax = 16;
 constexpr int64_t kHintedListMin = int64_t(1) << 18;  // taken whatever k is: 64 workgroups
+
+// Largest k whose list is first given to one workgroup (kTopkSmallList entries:
+// eight times this k).
+constexpr int64_t kHintedSmallK = 4096;
 
 bool topk_hint_key(const micro_ctx* ctx, double theta, int64_t k, int64_t len, uint32_t* key) {
     if (!ctx->has_staged || !ctx->d_stage || !ctx->d_tile_counts || !ctx->d_tile_sumsq) return false;
@@ -897,8 +901,8 @@ micro_status execute_step(micro_ctx* ctx, const float* grad, float* residual, in
         // that they do not apply, the host goes on from the list's length.
         // Wall time with a wait here, three passes with a select each, a trim
         // of four launches and the list always from 7/8 of the hint up, and
-        // now: ResNet-50 rank 0 89.7 and 55.9 us, BERT-large rank 3 223.5 and
-        // 134.6 us.
+        // now: ResNet-50 rank 0 85.5 and 41.3 us, BERT-large rank 3 218.8 and
+        // 126.8 us.
         const int64_t want = topk_count(density, len);
         micro::TopkHinted hs{};
         hs.count = ctx->d_count;
@@ -915,28 +919,35 @@ micro_status execute_step(micro_ctx* ctx, const float* grad, float* residual, in
         hs.epoch = a.epoch;
         hs.host = ctx->h_topk_dev;
         volatile int64_t* h = ctx->h_topk;
-        h[5] = 0;
-        if ((e = micro::launch_topk_hinted(hs, ctx->stream)) != hipSuccess)
-            return hip_fail(ctx, e, "top-k hinted select launch");
-        if (timed && (e = hipEventRecord(ctx->ev[1], ctx->stream)) != hipSuccess)
-            return hip_fail(ctx, e, "hipEventRecord");
-        if ((e = hipStreamSynchronize(ctx->stream)) != hipSuccess) return hip_fail(ctx, e, "hipStreamSynchronize");
-        const int64_t listed = host_count[0];
-        if (listed < 0 || listed > len) {
-            set_error(ctx, "device reported %lld listed of %lld", static_cast<long long>(listed),
-                      static_cast<long long>(len));
-            ctx->needs_reset = true;
-            return MICRO_EHIP;
+        // One workgroup first where k promises a list that it can hold; a
+        // longer one still goes to the others.
+        int64_t listed = 0;
+        for (bool small = want <= kHintedSmallK;; small = false) {
+            h[5] = 0;
+            e = small ? micro::launch_topk_hinted_small(hs, ctx->stream) : micro::launch_topk_hinted(hs, ctx->stream);
+            if (e != hipSuccess) return hip_fail(ctx, e, "top-k hinted select launch");
+            if (timed && (e = hipEventRecord(ctx->ev[1], ctx->stream)) != hipSuccess)
+                return hip_fail(ctx, e, "hipEventRecord");
+            if ((e = hipStreamSynchronize(ctx->stream)) != hipSuccess) return hip_fail(ctx, e, "hipStreamSynchronize");
+            listed = host_count[0];
+            if (listed < 0 || listed > len) {
+                set_error(ctx, "device reported %lld listed of %lld", static_cast<long long>(listed),
+                          static_cast<long long>(len));
+                ctx->needs_reset = true;
+                return MICRO_EHIP;
+            }
+            if (!small || h[5] == 1 || listed <= micro::kTopkSmallList || listed > hs.max_list) break;
         }
         if (h[5] == 1) {
             plan.route = TopkRoute::kHintList;
             plan.listed = listed;
             plan.kept = want;
             finished = true;
-            // twice the share by which the k-th magnitude fell, or half the
-            // last slack while it did not
-            const double fell = 1.0 - static_cast<double>(float_from_bits(static_cast<uint32_t>(h[0]))) / *theta;
-            ctx->topk_slack = std::min(kTopkSlackMax, std::max({kTopkSlackMin, 2.0 * fell, 0.5 * ctx->topk_slack}));
+            // three times the share by which the k-th magnitude moved, up or
+            // down, now or (fading) in the last steps
+            const double moved =
+                std::fabs(1.0 - static_cast<double>(float_from_bits(static_cast<uint32_t>(h[0]))) / *theta);
+            ctx->topk_slack = std::min(kTopkSlackMax, std::max({kTopkSlackMin, 3.0 * moved, 0.8 * ctx->topk_slack}));
         } else {
             if (listed < want) ctx->topk_slack = kTopkSlackMax;
             const micro_status s = topk_after_hint(ctx, &plan, listed, residual, start, len, density, out_idx, out_val);

@@ -147,6 +147,12 @@ struct TopkHinted {
 };
 hipError_t launch_topk_hinted(const TopkHinted& args, hipStream_t stream);
 
+// The hinted select by one workgroup that holds the whole list in registers:
+// lists of up to kTopkSmallList entries (max_list and, beyond status 4's
+// reasons above, words, status and epoch are not used).
+constexpr int64_t kTopkSmallList = 32768;
+hipError_t launch_topk_hinted_small(const TopkHinted& args, hipStream_t stream);
+
 // Writes the output list [0, n) back into the residual: residual[idx[j]] =
 // val[j] for every idx[j] in [start, end) (the rest is skipped).  After the
 // threshold step the residual then holds acc over the whole partition (the

@@ -842,6 +842,151 @@ __global__ __launch_bounds__(kTrimBlock) void topk_hinted_trim_kernel(TopkHinted
     }
 }
 
+// The hinted select and the trim by one workgroup.  A short list is bound by
+// launches and by each launch's first loads: on ResNet-50 rank 0's list the
+// three kernels above take 18 us and two launch gaps, this one 14 us or less
+// (the step 52.2 us of wall time with them, 41.3 with this one and the closer
+// bound that shortens the list).  Every entry is in registers, index and value, before the first
+// store (the wait and the barriers between), so the list is compacted in place.
+constexpr int kSmallBlock = 1024;
+constexpr int kSmallPer = static_cast<int>(kTopkSmallList) / kSmallBlock;
+__global__ __launch_bounds__(kSmallBlock) void topk_hinted_small_kernel(TopkHinted a) {
+    constexpr int WAVES = kSmallBlock / kWave;
+    constexpr int COUNTS = kSmallPer * WAVES;      // one (row, wavefront) count each
+    constexpr int FINE_PER = kTopkFine / kSmallBlock;
+    static_assert(COUNTS <= kSmallBlock, "one count a thread in the scan");
+    static_assert(kTopkSmallList < (1 << 16), "two counts in one word");
+    __shared__ uint32_t s_fine[kTopkFine];
+    __shared__ uint32_t s_bins[kTopkWindowBins + 1];
+    __shared__ uint32_t s_cnt[COUNTS];             // greater in the low half, equal in the high half
+    __shared__ uint32_t s_wave[WAVES], s_found[3];
+    const int tid = threadIdx.x;
+    const int lane = tid & (kWave - 1);
+    const int wave = tid / kWave;
+    const int64_t count = a.count[0];
+    if (count < static_cast<int64_t>(a.k) || count > kTopkSmallList) {  // uniform
+        if (tid == 0) a.host[5] = 4;
+        return;
+    }
+    const int n = static_cast<int>(count);
+    float val[kSmallPer];
+    int32_t idx[kSmallPer];
+#pragma unroll
+    for (int j = 0; j < kSmallPer; ++j) {
+        if (j * kSmallBlock < n) {  // uniform
+            const int p = j * kSmallBlock + tid;
+            val[j] = a.out_val[p < n ? p : n - 1];
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < kSmallPer; ++j) {
+        if (j * kSmallBlock < n) {  // uniform
+            const int p = j * kSmallBlock + tid;
+            idx[j] = a.out_idx[p < n ? p : n - 1];
+        }
+    }
+    for (int i = tid; i < kTopkFine; i += kSmallBlock) s_fine[i] = 0u;
+    if (tid < kTopkWindowBins + 1) s_bins[tid] = 0u;
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < kSmallPer; ++j) {
+        if (j * kSmallBlock < n && j * kSmallBlock + tid < n) {
+            const uint32_t bin = (key_of(val[j]) - a.key_floor) >> kTopkFineBits;
+            atomicAdd(&s_bins[bin < kTopkWindowBins ? bin : kTopkWindowBins], 1u);
+        }
+    }
+    __syncthreads();
+    const uint32_t over = s_bins[kTopkWindowBins];
+    if (over >= a.k) {  // uniform: the k-th key is above the bins
+        if (tid == 0) a.host[5] = 4;
+        return;
+    }
+    uint32_t bin, above, in_bin;
+    find_from_top<kSmallBlock, kTopkWindowBins, 1>(s_bins, a.k - over, s_wave, s_found, &bin, &above, &in_bin);
+    const uint32_t rank = a.k - over - above;
+#pragma unroll
+    for (int j = 0; j < kSmallPer; ++j) {
+        if (j * kSmallBlock < n && j * kSmallBlock + tid < n) {
+            const uint32_t off = key_of(val[j]) - a.key_floor;
+            if ((off >> kTopkFineBits) == bin) atomicAdd(&s_fine[off & (kTopkFine - 1)], 1u);
+        }
+    }
+    __syncthreads();
+    {  // the k-th key among the bin's counters, FINE_PER a thread, from the top
+        const int top = kTopkFine - 1 - tid * FINE_PER;
+        uint32_t mine = 0;
+#pragma unroll
+        for (int i = 0; i < FINE_PER; ++i) mine += s_fine[top - i];
+        uint32_t total;
+        uint32_t before = block_inclusive_sum<kSmallBlock>(mine, s_wave, &total) - mine;
+        if (before < rank && rank <= before + mine) {
+#pragma unroll 1
+            for (int i = 0; i < FINE_PER; ++i) {
+                const uint32_t c = s_fine[top - i];
+                if (before + c >= rank) {
+                    s_found[0] = top - i;
+                    s_found[1] = before;
+                    s_found[2] = c;
+                    break;
+                }
+                before += c;
+            }
+        }
+        __syncthreads();
+    }
+    const uint32_t key = a.key_floor + (bin << kTopkFineBits) + s_found[0];
+    const uint32_t keep = rank - s_found[1];
+    if (tid == 0) {
+        a.host[0] = key;
+        a.host[1] = over + above + s_found[1];
+        a.host[2] = s_found[2];
+        a.host[3] = keep;
+        a.host[4] = n;
+        a.host[5] = 1;
+    }
+#pragma unroll
+    for (int j = 0; j < kSmallPer; ++j) {
+        uint32_t c = 0;
+        if (j * kSmallBlock < n) {  // uniform
+            const uint32_t kv = j * kSmallBlock + tid < n ? key_of(val[j]) : 0u;
+            c = static_cast<uint32_t>(__popcll(__ballot(kv > key))) |
+                static_cast<uint32_t>(__popcll(__ballot(kv == key))) << 16;
+        }
+        if (lane == 0) s_cnt[j * WAVES + wave] = c;
+    }
+    __builtin_amdgcn_s_waitcnt(0x0F70);  // vector-memory count 0: the indices have arrived too
+    __syncthreads();
+    {
+        const uint32_t own = tid < COUNTS ? s_cnt[tid] : 0u;
+        uint32_t total;
+        const uint32_t incl = block_inclusive_sum<kSmallBlock>(own, s_wave, &total);
+        if (tid < COUNTS) s_cnt[tid] = incl - own;
+    }
+    __syncthreads();
+    const uint64_t lower_lanes = lane ? (~0ull >> (kWave - lane)) : 0ull;
+#pragma unroll
+    for (int j = 0; j < kSmallPer; ++j) {
+        if (j * kSmallBlock >= n) break;  // uniform
+        const int p = j * kSmallBlock + tid;
+        const uint32_t kv = p < n ? key_of(val[j]) : 0u;
+        const uint64_t mg = __ballot(kv > key), mt = __ballot(kv == key);
+        if (p >= n) continue;
+        const uint32_t before = s_cnt[j * WAVES + wave];
+        const uint32_t g = (before & 0xffffu) + static_cast<uint32_t>(__popcll(mg & lower_lanes));
+        const uint32_t t = (before >> 16) + static_cast<uint32_t>(__popcll(mt & lower_lanes));
+        if (kv > key || (kv == key && t < keep)) {
+            if (kv < a.zero_key) a.residual[idx[j]] = 0.0f;
+            const uint32_t to = g + (t < keep ? t : keep);
+            if (to != static_cast<uint32_t>(p)) {
+                a.out_idx[to] = idx[j];
+                a.out_val[to] = val[j];
+            }
+        } else if (kv >= a.zero_key) {
+            a.residual[idx[j]] = val[j];
+        }
+    }
+}
+
 // Writes the output list back into the residual (one entry a thread, grid
 // stride); indices outside [start, end) are skipped.
 __global__ __launch_bounds__(kTrimBlock) void topk_restore_kernel(const int32_t* out_idx, const float* out_val,
@@ -1062,6 +1207,13 @@ hipError_t launch_topk_hinted(const TopkHinted& a, hipStream_t stream) {
     hipLaunchKernelGGL(topk_hinted_bins_kernel, dim3(bins_blocks), dim3(kTopkHistBlock), 0, stream, a);
     hipLaunchKernelGGL(topk_hinted_keys_kernel, dim3(keys_blocks), dim3(kTopkKeysBlock), 0, stream, a);
     hipLaunchKernelGGL(topk_hinted_trim_kernel, dim3(static_cast<uint32_t>(chunks)), dim3(kTrimBlock), 0, stream, a);
+    return hipGetLastError();
+}
+
+hipError_t launch_topk_hinted_small(const TopkHinted& a, hipStream_t stream) {
+    if (!a.count || !a.out_idx || !a.out_val || !a.residual || !a.host || a.k < 1 || a.key_floor > kTopkKeyMax)
+        return hipErrorInvalidValue;
+    hipLaunchKernelGGL(topk_hinted_small_kernel, dim3(1), dim3(kSmallBlock), 0, stream, a);
     return hipGetLastError();
 }
 

@@ -524,19 +524,21 @@ def test_build_up_of_the_comparators_and_its_absence_under_micro():
 
 
 @pytest.mark.parametrize("variant", [AUTO, STAGED], ids=["auto", "staged"])
+@pytest.mark.parametrize("k", [2_400, 6_000])  # one workgroup takes the list first up to k = 4096
 @pytest.mark.parametrize("listed,k_rank", [
     (0, 0), (1, 0),              # the list holds exactly k values, and one more
     (4095, 0), (4096, 0), (4097, 0),  # k and a chunk boundary of the trim
     (20_000, 1),                 # the k-th magnitude tied across chunks, some of the ties dropped
     (20_000, 2),                 # the k-th magnitude above the counted keys: the passes take over
+    (32_768 - 2_400, 0), (32_769 - 2_400, 0),  # the longest list of the one workgroup (k = 2400), and one more
     (270_000, 0),                # a list longer than the hinted select takes
 ])
-def test_hinted_select_at_its_limits(variant, listed, k_rank):
+def test_hinted_select_at_its_limits(variant, listed, k_rank, k):
     """A partition whose list under a hint of 1 holds k + `listed` values: at
     the edges of the hinted select (fewest values, whole chunks, ties cut
-    between chunks, the counted keys' end, the longest list), the one-launch
+    between chunks, the counted keys' end, the longest lists), the one-launch
     and the staged step; two calls in a row, so the counters are clear again."""
-    N, k = 2_400_000, 2_400
+    N = 2_400_000
     rng = np.random.default_rng(listed * 3 + k_rank)
     g = np.zeros(N, np.float32)
     at = rng.permutation(N)
@@ -555,6 +557,6 @@ def test_hinted_select_at_its_limits(variant, listed, k_rank):
     note(f"hinted select limits listed={listed} k_rank={k_rank} variant={variant}")
     sp = make(N, variant)
     for _ in range(2):
-        topk_vs_oracle(g, res, 0, 1, 0.001, variant, sp=sp, hint=1.0)
+        topk_vs_oracle(g, res, 0, 1, (k + 0.5) / N, variant, sp=sp, hint=1.0)
         assert sp.last_topk_route() == micro.MICRO_TOPK_ROUTE_HINT_LIST
     sp.close()
