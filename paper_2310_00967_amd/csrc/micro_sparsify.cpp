@@ -420,8 +420,9 @@ float f32_at_or_below(double x) {
 constexpr int64_t kHintedListMax = 16;
 constexpr int64_t kHintedListMin = int64_t(1) << 18;  // taken whatever k is: 64 workgroups
 
-// Largest k whose list is first given to one workgroup (kTopkSmallList entries:
-// eight times this k).
+// Largest k whose list is first given to one workgroup (kTopkSmallList entries,
+// four times this k; 16 a thread: with 32 the compiler spilled registers and
+// the kernel took 34 us instead of 8.9).
 constexpr int64_t kHintedSmallK = 4096;
 
 bool topk_hint_key(const micro_ctx* ctx, double theta, int64_t k, int64_t len, uint32_t* key) {
@@ -901,8 +902,8 @@ micro_status execute_step(micro_ctx* ctx, const float* grad, float* residual, in
         // that they do not apply, the host goes on from the list's length.
         // Wall time with a wait here, three passes with a select each, a trim
         // of four launches and the list always from 7/8 of the hint up, and
-        // now: ResNet-50 rank 0 85.5 and 41.3 us, BERT-large rank 3 218.8 and
-        // 126.8 us.
+        // now: ResNet-50 rank 0 88 and 36.4 us, BERT-large rank 3 218.8 and
+        // 124.4 us.
         const int64_t want = topk_count(density, len);
         micro::TopkHinted hs{};
         hs.count = ctx->d_count;

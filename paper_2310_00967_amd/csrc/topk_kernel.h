@@ -113,8 +113,11 @@ hipError_t launch_topk_trim(int32_t* out_idx, float* out_val, float* residual, i
 // where the list is shorter than k or longer than max_list, or the k-th key
 // lies above the bins (1.25 to 1.5 times key_floor's magnitude, by its
 // mantissa): the caller then goes on with the list as it is.
-constexpr int kTopkWindowBins = 256;
-constexpr uint32_t kTopkFineBits = 14;  // 2^14 counters are 64 KB of LDS
+// 1024 bins of 4096 keys: the one workgroup of launch 2 or 3 that clears, scans
+// and adds a bin's counters has few of them (256 bins of 16,384 keys: launch 2
+// 9.8 us on BERT-large rank 3's list, now 5.8).
+constexpr int kTopkWindowBins = 1024;
+constexpr uint32_t kTopkFineBits = 12;
 constexpr uint32_t kTopkGroupBits = 7;
 constexpr int kTopkFine = 1 << kTopkFineBits;
 constexpr int kTopkGroups = kTopkFine >> kTopkGroupBits;
@@ -123,7 +126,7 @@ constexpr int kTopkGroupStride = 32;    // a group counter to a 128-byte line: m
 // 3), the key and the group counters (cleared by launch 1), then the state of
 // launch 2
 constexpr int kTopkHintedBins = 0;
-constexpr int kTopkHintedFine = 512;
+constexpr int kTopkHintedFine = 1088;
 constexpr int kTopkHintedGroups = kTopkHintedFine + kTopkFine;
 constexpr int kTopkHintedState = kTopkHintedGroups + kTopkGroups * kTopkGroupStride;
 constexpr int kTopkHintedWords = kTopkHintedState + 8;
@@ -150,7 +153,7 @@ hipError_t launch_topk_hinted(const TopkHinted& args, hipStream_t stream);
 // The hinted select by one workgroup that holds the whole list in registers:
 // lists of up to kTopkSmallList entries (max_list and, beyond status 4's
 // reasons above, words, status and epoch are not used).
-constexpr int64_t kTopkSmallList = 32768;
+constexpr int64_t kTopkSmallList = 16384;
 hipError_t launch_topk_hinted_small(const TopkHinted& args, hipStream_t stream);
 
 // Writes the output list [0, n) back into the residual: residual[idx[j]] =

@@ -589,8 +589,8 @@ __device__ __forceinline__ void for_each_key(const float* list, int64_t n, F f) 
 
 // Launch 1.  Each wavefront counts in a copy of its own in LDS; the workgroup
 // adds the nonzero sums to the global counters, so the pass is bound by
-// workgroups times nonzero bins of global atomics and takes few of both
-// (BERT-large rank 3's list 6.4 us, ResNet-50 rank 0's 4.3 us).
+// workgroups times lines of nonzero bins and takes few of both (BERT-large
+// rank 3's list 6.6 us).
 __global__ __launch_bounds__(kTopkHistBlock) void topk_hinted_bins_kernel(TopkHinted a) {
     constexpr int WAVES = kTopkHistBlock / kWave;
     constexpr int BINS = kTopkWindowBins + 1;
@@ -732,7 +732,7 @@ __device__ __forceinline__ uint32_t hinted_lookback(const uint64_t* status, uint
 }
 
 // Launch 3, bound by the scattered residual stores and the look-back (BERT-large
-// rank 3's list 13.4 us, where the four launches of the trim took 25.4 us and
+// rank 3's list 10.4 us, where the four launches of the trim took 25.4 us and
 // the gaps between them).  A chunk's entries are all in registers, index and value, before
 // its counts are published (the wait and the barrier below), and a chunk
 // stores only once the counts of every chunk before it are published, to
@@ -844,9 +844,9 @@ __global__ __launch_bounds__(kTrimBlock) void topk_hinted_trim_kernel(TopkHinted
 
 // The hinted select and the trim by one workgroup.  A short list is bound by
 // launches and by each launch's first loads: on ResNet-50 rank 0's list the
-// three kernels above take 18 us and two launch gaps, this one 14 us or less
-// (the step 52.2 us of wall time with them, 41.3 with this one and the closer
-// bound that shortens the list).  Every entry is in registers, index and value, before the first
+// three kernels above take 18 us and two launch gaps, this one 8.9 us (the step
+// 52.2 us of wall time with them, 36.4 with this one and the closer bound that
+// shortens the list).  Every entry is in registers, index and value, before the first
 // store (the wait and the barriers between), so the list is compacted in place.
 constexpr int kSmallBlock = 1024;
 constexpr int kSmallPer = static_cast<int>(kTopkSmallList) / kSmallBlock;
@@ -886,7 +886,7 @@ __global__ __launch_bounds__(kSmallBlock) void topk_hinted_small_kernel(TopkHint
         }
     }
     for (int i = tid; i < kTopkFine; i += kSmallBlock) s_fine[i] = 0u;
-    if (tid < kTopkWindowBins + 1) s_bins[tid] = 0u;
+    for (int i = tid; i < kTopkWindowBins + 1; i += kSmallBlock) s_bins[i] = 0u;
     __syncthreads();
 #pragma unroll
     for (int j = 0; j < kSmallPer; ++j) {
@@ -1200,10 +1200,10 @@ hipError_t launch_topk_hinted(const TopkHinted& a, hipStream_t stream) {
     const int64_t chunks = (a.max_list + kTopkTrimChunk - 1) / kTopkTrimChunk;
     if (chunks > 0x7FFFFFFFll) return hipErrorInvalidValue;
     // sixteen values a thread of a list of twice k entries, at most 512
-    // workgroups of 256 threads and 256 of 1024 (64 KB of LDS each)
+    // workgroups of 256 threads and 256 of 1024
     const int64_t want = (2ll * a.k + 4095) / 4096;
     const uint32_t bins_blocks = static_cast<uint32_t>(want < 512 ? want : 512);
-    const uint32_t keys_blocks = static_cast<uint32_t>(want < 1024 ? (want + 3) / 4 : 256);
+    const uint32_t keys_blocks = static_cast<uint32_t>(want < 256 ? want : 256);
     hipLaunchKernelGGL(topk_hinted_bins_kernel, dim3(bins_blocks), dim3(kTopkHistBlock), 0, stream, a);
     hipLaunchKernelGGL(topk_hinted_keys_kernel, dim3(keys_blocks), dim3(kTopkKeysBlock), 0, stream, a);
     hipLaunchKernelGGL(topk_hinted_trim_kernel, dim3(static_cast<uint32_t>(chunks)), dim3(kTrimBlock), 0, stream, a);

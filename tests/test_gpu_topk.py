@@ -530,7 +530,7 @@ def test_build_up_of_the_comparators_and_its_absence_under_micro():
     (4095, 0), (4096, 0), (4097, 0),  # k and a chunk boundary of the trim
     (20_000, 1),                 # the k-th magnitude tied across chunks, some of the ties dropped
     (20_000, 2),                 # the k-th magnitude above the counted keys: the passes take over
-    (32_768 - 2_400, 0), (32_769 - 2_400, 0),  # the longest list of the one workgroup (k = 2400), and one more
+    (16_384 - 2_400, 0), (16_385 - 2_400, 0),  # the longest list of the one workgroup (k = 2400), and one more
     (270_000, 0),                # a list longer than the hinted select takes
 ])
 def test_hinted_select_at_its_limits(variant, listed, k_rank, k):
