@@ -107,6 +107,14 @@ constexpr int64_t kAutoTicketMax = int64_t(1) << 20;
 // the look-back's contention costs more than a second launch.
 constexpr int64_t kOnePassMax = int64_t(1) << 22;
 
+// Most values outside the partition that a full pass accumulates in the
+// one-launch step's launch.  Wall time of a pass in one launch and in two:
+// 1.1M values (half of them searched) 18.3 and 21.4 us, 8.0M 31.3 and 36.6,
+// ResNet-18's 11.7M (a 16th searched) 36.4 and 39.7, 60M 131.9 and 132.8, but
+// 335M (a 128th) 733 and 678: the accumulating kernel's own workgroups stream
+// faster.
+constexpr int64_t kPassAccumulateMax = int64_t(1) << 26;
+
 // Tiles of the largest one-launch partition whose dense rows are counted.
 constexpr int64_t kDenseTiles = kOnePassMax / (micro::kPassRowsMid * micro::kPassRow) + 2;
 
@@ -776,20 +784,6 @@ micro_status execute_step(micro_ctx* ctx, const float* grad, float* residual, in
         if (s != MICRO_OK) return s;
     }
     const bool vec4 = ((reinterpret_cast<uintptr_t>(grad) ^ reinterpret_cast<uintptr_t>(residual)) & 15u) == 0;
-    micro::AccumulateArgs acc{};
-    if (n_outside > 0) {
-        acc.grad = grad;
-        acc.residual = residual;
-        const int64_t lo[2] = {0, start + len}, hi[2] = {start, ctx->n_total};
-        for (int r = 0; r < 2; ++r) {
-            acc.start[r] = lo[r];
-            acc.end[r] = hi[r];
-            acc.base[r] = micro::tile_base_for(grad, lo[r], vec4);
-            acc.tiles[r] = hi[r] > lo[r] ? static_cast<uint32_t>((hi[r] - acc.base[r] + micro::kStreamTile - 1) /
-                                                                  micro::kStreamTile)
-                                         : 0u;
-        }
-    }
     // AUTO contexts run partitions of up to kOnePassMax values in one launch
     // and the staged schedule above, or above kAutoTicketMax where the scan
     // pass is asked for on its own.
@@ -799,6 +793,24 @@ micro_status execute_step(micro_ctx* ctx, const float* grad, float* residual, in
     const bool reports_staged = ctx->has_staged && !(ctx->has_one_pass && len <= kAutoTicketMax);
     const int rows = micro::pass_rows_for(len);
     const int64_t tile_elems = staged ? micro::kStreamTile : static_cast<int64_t>(rows) * micro::kPassRow;
+    // What the pass accumulates outside the partition: in the one-pass launch
+    // up to four-row tiles, else in a launch of its own before the step's.
+    const bool acc_in_pass = n_outside > 0 && n_outside <= kPassAccumulateMax && len > 0 && !staged &&
+                             rows <= micro::kPassRowsMid;
+    micro::AccumulateArgs acc{};
+    if (n_outside > 0) {
+        const int64_t acc_tile = acc_in_pass ? micro::kPassRowsMid * micro::kPassRow : micro::kStreamTile;
+        acc.grad = grad;
+        acc.residual = residual;
+        const int64_t lo[2] = {0, start + len}, hi[2] = {start, ctx->n_total};
+        for (int r = 0; r < 2; ++r) {
+            acc.start[r] = lo[r];
+            acc.end[r] = hi[r];
+            acc.base[r] = acc_in_pass ? micro::tile_base_for(residual, lo[r], true)
+                                      : micro::tile_base_for(grad, lo[r], vec4);
+            acc.tiles[r] = hi[r] > lo[r] ? static_cast<uint32_t>((hi[r] - acc.base[r] + acc_tile - 1) / acc_tile) : 0u;
+        }
+    }
     micro::LaunchArgs a{};
     a.grad = grad;
     a.residual = residual;
@@ -880,14 +892,14 @@ micro_status execute_step(micro_ctx* ctx, const float* grad, float* residual, in
     volatile int64_t* host_count = ctx->h_count;  // stored by the last kernel of the step
     host_count[0] = len > 0 ? -1 : 0;
     host_count[1] = len > 0 ? -1 : 0;
-    if (n_outside > 0 && (e = micro::launch_accumulate(acc, vec4, ctx->stream)) != hipSuccess)
+    if (n_outside > 0 && !acc_in_pass && (e = micro::launch_accumulate(acc, vec4, ctx->stream)) != hipSuccess)
         return hip_fail(ctx, e, "accumulate kernel launch");
     // The staged schedule's stream and scan kernels run as one launch unless
     // the caller asked for the scan on its own.
     const bool fused = staged && !separate;
     if (len > 0) {
         ctx->epoch = a.epoch;
-        e = !staged ? micro::launch_one_pass(a, rows, ctx->stream)
+        e = !staged ? micro::launch_one_pass(a, rows, acc_in_pass ? &acc : nullptr, ctx->stream)
             : fused ? micro::launch_fused(a, vec4, ctx->stream)
                     : micro::launch_staged(a, vec4, ctx->stream);
         if (e != hipSuccess) return hip_fail(ctx, e, "sparsify kernel launch");
@@ -950,7 +962,8 @@ micro_status execute_step(micro_ctx* ctx, const float* grad, float* residual, in
                 std::fabs(1.0 - static_cast<double>(float_from_bits(static_cast<uint32_t>(h[0]))) / *theta);
             ctx->topk_slack = std::min(kTopkSlackMax, std::max({kTopkSlackMin, 3.0 * moved, 0.8 * ctx->topk_slack}));
         } else {
-            if (listed < want) ctx->topk_slack = kTopkSlackMax;
+            // too few listed, or too many
+            ctx->topk_slack = listed < want ? kTopkSlackMax : std::max(kTopkSlackMin, 0.5 * ctx->topk_slack);
             const micro_status s = topk_after_hint(ctx, &plan, listed, residual, start, len, density, out_idx, out_val);
             if (s != MICRO_OK) return s;
         }
@@ -1293,7 +1306,7 @@ micro_status micro_sparsify_step_noalloc(const float* grad, float* residual, int
     a.status = dv.words + micro::kStaticHeaderWords;
     a.group_status = a.status + micro::kStaticMaxTiles;
     a.epoch = dv.epoch + 1;
-    if ((e = micro::launch_one_pass(a, rows, stream)) != hipSuccess) return noalloc_fail(dv, e, "sparsify kernel launch");
+    if ((e = micro::launch_one_pass(a, rows, nullptr, stream)) != hipSuccess) return noalloc_fail(dv, e, "sparsify kernel launch");
     dv.epoch = a.epoch;
     int64_t selected = -1;
     // One copy in stream order that the host waits for: the kernel has finished

@@ -160,9 +160,10 @@ struct LaunchArgs {
 
 // Error-feedback accumulation outside the searched partition (Algorithm 1,
 // every element accumulates its new gradient): residual = grad + residual
-// over ranges [start[r], end[r]), r = 0, 1, in tiles of kStreamTile values
-// whose first tile starts at base[r] (<= start[r]); workgroups
-// [0, tiles[0]) take range 0, the next tiles[1] range 1.
+// over ranges [start[r], end[r]), r = 0, 1, in tiles of kStreamTile values (of
+// kPassRowsMid rows in the one-pass launch) whose first tile starts at base[r]
+// (<= start[r]); workgroups [0, tiles[0]) take range 0, the next tiles[1]
+// range 1.
 struct AccumulateArgs {
     const float* grad;
     float* residual;
@@ -189,7 +190,10 @@ hipError_t launch_fused(const LaunchArgs& args, bool vec4, hipStream_t stream);
 // The one-pass schedule with tiles of `rows` rows (pass_rows_for); a.base from
 // tile_base_for(residual, start, true).  theta_zero above theta_f is honoured
 // with kPassRowsMid rows only.
-hipError_t launch_one_pass(const LaunchArgs& args, int rows, hipStream_t stream);
+// With acc, the same launch accumulates its ranges too (of the same vectors;
+// tiles of kPassRowsMid rows, their bases from tile_base_for(residual, ...)):
+// up to kPassRowsMid rows.
+hipError_t launch_one_pass(const LaunchArgs& args, int rows, const AccumulateArgs* acc, hipStream_t stream);
 // The sweep: num_tiles / num_chunks are the totals over the table's segments.
 // fused: the stream and scan passes in one launch of num_tiles + num_chunks
 // workgroups, each segment's workgroups from its wg_first on as fused_role

@@ -1434,7 +1434,7 @@ __device__ __forceinline__ uint32_t pass_offset_of(const LaunchArgs& a, uint32_t
 // 190 and 118 us, 400M 1.49 and 0.91 ms.
 // HINT: only the residual of values at or above theta_zero becomes +0.
 template <int ROWS, bool HINT>
-__global__ __launch_bounds__(kPassBlock) void one_pass_kernel(LaunchArgs a) {
+__device__ __forceinline__ void one_pass_tile(const LaunchArgs& a) {
     constexpr int WAVES = kPassStream / kWaveSize;
     constexpr int32_t TILE = ROWS * kPassRow;
     __shared__ uint32_t s_wave_total[ROWS * WAVES];
@@ -1523,6 +1523,39 @@ __global__ __launch_bounds__(kPassBlock) void one_pass_kernel(LaunchArgs a) {
         a.host_count[0] = static_cast<int64_t>(excl) + count;
         a.host_count[1] = 0;
     }
+}
+
+template <int ROWS, bool HINT>
+__global__ __launch_bounds__(kPassBlock) void one_pass_kernel(LaunchArgs a) {
+    one_pass_tile<ROWS, HINT>(a);
+}
+
+// The one-launch step of a full error-feedback pass: the searched tiles first,
+// then workgroups that accumulate the rest of the vector, four rows each, while
+// the tiles wait for their loads and their look-back: a launch and the step's
+// latency less (ResNet-18's pass 36.4 us of wall time, 39.7 in two launches).
+template <int ROWS, bool HINT>
+__global__ __launch_bounds__(kPassBlock) void one_pass_accumulate_kernel(LaunchArgs a, AccumulateArgs acc) {
+    constexpr int ACC_ROWS = kPassRowsMid;
+    if (blockIdx.x < a.num_tiles) {
+        one_pass_tile<ROWS, HINT>(a);
+        return;
+    }
+    const uint32_t tid = threadIdx.x;
+    if (tid >= kPassStream) return;
+    uint32_t tile = blockIdx.x - a.num_tiles;
+    int r = 0;
+    if (tile >= acc.tiles[0]) {
+        tile -= acc.tiles[0];
+        r = 1;
+    }
+    constexpr int32_t TILE = ACC_ROWS * kPassRow;
+    PassTile<ACC_ROWS> t;
+    t.base = acc.base[r] + static_cast<int64_t>(tile) * TILE;
+    t.lo = t.base < acc.start[r] ? static_cast<int32_t>(acc.start[r] - t.base) : 0;
+    t.hi = t.base + TILE > acc.end[r] ? static_cast<int32_t>(acc.end[r] - t.base) : TILE;
+    pass_load<ACC_ROWS>(a, t, tid);
+    pass_store<ACC_ROWS>(a, t, tid, 0u);
 }
 
 // ---------------------------------------------------------------------------
@@ -1668,20 +1701,34 @@ hipError_t launch_sweep(const LaunchArgs& args, const SweepTable& table, bool ve
     return hipGetLastError();
 }
 
-hipError_t launch_one_pass(const LaunchArgs& args, int rows, hipStream_t stream) {
+namespace {
+
+template <int ROWS, bool HINT>
+void launch_pass(const LaunchArgs& args, const AccumulateArgs* acc, hipStream_t stream) {
+    const dim3 block(kPassBlock);
+    if (acc)
+        hipLaunchKernelGGL((one_pass_accumulate_kernel<ROWS, HINT>),
+                           dim3(args.num_tiles + acc->tiles[0] + acc->tiles[1]), block, 0, stream, args, *acc);
+    else
+        hipLaunchKernelGGL((one_pass_kernel<ROWS, HINT>), dim3(args.num_tiles), block, 0, stream, args);
+}
+
+}  // namespace
+
+hipError_t launch_one_pass(const LaunchArgs& args, int rows, const AccumulateArgs* acc, hipStream_t stream) {
     if (!all_set(args.grad, args.residual, args.out_idx, args.out_val, args.count_out, args.host_count, args.status,
                  args.group_status))
         return hipErrorInvalidValue;
-    const dim3 grid(args.num_tiles), block(kPassBlock);
     if (args.theta_zero > args.theta_f) {
         if (rows != kPassRowsMid) return hipErrorInvalidValue;
-        hipLaunchKernelGGL((one_pass_kernel<kPassRowsMid, true>), grid, block, 0, stream, args);
+        launch_pass<kPassRowsMid, true>(args, acc, stream);
     } else if (rows == kPassRowsSmall) {
-        hipLaunchKernelGGL((one_pass_kernel<kPassRowsSmall, false>), grid, block, 0, stream, args);
+        launch_pass<kPassRowsSmall, false>(args, acc, stream);
     } else if (rows == kPassRowsMid) {
-        hipLaunchKernelGGL((one_pass_kernel<kPassRowsMid, false>), grid, block, 0, stream, args);
-    } else if (rows == kPassRowsLarge) {
-        hipLaunchKernelGGL((one_pass_kernel<kPassRowsLarge, false>), grid, block, 0, stream, args);
+        launch_pass<kPassRowsMid, false>(args, acc, stream);
+    } else if (rows == kPassRowsLarge && !acc) {
+        hipLaunchKernelGGL((one_pass_kernel<kPassRowsLarge, false>), dim3(args.num_tiles), dim3(kPassBlock), 0, stream,
+                           args);
     } else {
         return hipErrorInvalidValue;
     }

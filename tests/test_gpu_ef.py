@@ -410,3 +410,48 @@ def test_ef_local_error_needs_the_staged_schedule():
         sp.ef_step(g, r, 0, 0, 2, 0.1, 1.0, local_error=True)
     assert not bool(r.any())
     sp.close()
+
+
+@pytest.mark.parametrize("N,world", [
+    (1, 1), (5, 2), (4_100, 3),
+    (2 * (1 << 19) - 1, 2),     # one-row searched tiles
+    (2 * (1 << 19) + 2, 2),     # four-row ones
+    (3 * 700_001, 3),
+    ((1 << 26) + (1 << 20), 64),       # the most accumulated in the step's launch (a 64th of it searched)
+    ((1 << 26) + (1 << 22) + 65, 64),  # more: a launch of its own
+])
+@pytest.mark.parametrize("shift", [0, 1])
+def test_pass_in_one_launch(N, world, shift):
+    """The full pass whose partition runs in one launch, with what lies before
+    and after the partition (nothing before the first, nothing after the last)
+    accumulated in the same launch or, past its limit, in another: the oracle's
+    bits for the first, a middle and the last partition, under the threshold rule and
+    the hinted top-k, with grad and residual at the same and at different
+    16-byte phases."""
+    note(f"one-launch pass N={N} world={world} shift={shift}")
+    rng = np.random.default_rng(N % 1009 + world)
+    g = rng.standard_normal(N, dtype=np.float32)
+    g[N // 4:N // 4 + 20_000] *= 30.0
+    res0 = rng.standard_normal(N, dtype=np.float32)
+    gbuf = torch.empty(N + 4, dtype=torch.float32, device=DEV)
+    g_dev = gbuf[shift:shift + N]
+    g_dev.copy_(torch.from_numpy(g))
+    big = N > 1 << 26
+    for rule in ((micro.MICRO_RULE_PROPORTIONAL,) if big else (micro.MICRO_RULE_PROPORTIONAL, micro.MICRO_RULE_TOPK)):
+        sp = micro.Sparsifier(N, device=DEV, rule=rule)
+        for worker in ([world // 2] if big else sorted({0, world // 2, world - 1})):
+            r_or = res0.copy()
+            if rule == micro.MICRO_RULE_TOPK:
+                theta = oracle.topk_ef_step(g, res0.copy(), 0, worker, world, 0.01, 1.0)[3]  # an exact hint
+                o_idx, o_val, k_or, th_or, c_or = oracle.topk_ef_step(g, r_or, 0, worker, world, 0.01, theta)
+            else:
+                theta = 3.0
+                o_idx, o_val, k_or, th_or, c_or = oracle.ef_step(g, r_or, 0, worker, world, 0.01, theta)[:5]
+            r_dev = torch.from_numpy(res0).to(DEV)
+            k, th, c, idx, val = sp.ef_step(g_dev, r_dev, 0, worker, world, 0.01, theta)
+            where = (N, world, worker, rule)
+            assert (k, th, c) == (k_or, th_or, c_or), where
+            assert np.array_equal(idx.cpu().numpy(), o_idx), where
+            assert first_mismatch(val.cpu().numpy(), o_val) < 0, where
+            assert first_mismatch(r_dev.cpu().numpy(), r_or) < 0, where
+        sp.close()
