@@ -921,10 +921,11 @@ def main_path(args, w, head, pool, n_pool, sp):
                                                       sources=TOPK_SOURCES)
                                          if args.topk_hint == "last" else None),
                              "kernel": "the threshold step at 7/8 of the incoming theta (the last step's k-th "
-                                       "magnitude), the wait, three topk_hist_kernel + topk_select_kernel passes "
-                                       "over its output list and the trim (route_series 3; 4: the list fell short "
-                                       "and the passes and the pick ran over the residual; 1 and 2: no hint, the "
-                                       "passes over the partition first); event-timed together",
+                                       "magnitude) or closer, topk_hinted_bins_kernel + topk_hinted_keys_kernel + "
+                                       "topk_hinted_trim_kernel (or topk_hinted_small_kernel) over its output list "
+                                       "(route_series 3; 4: the list fell short and the histogram passes and the "
+                                       "pick ran over the residual; 1 and 2: no hint, the passes over the partition "
+                                       "first); event-timed together",
                              "kernel_ms_avg": tk["kernel_ms_avg"], "alg_bytes_per_launch": tk["alg_bytes_per_launch"]},
                 "topk_over_threshold_step_time": (tk["kernel_ms_avg"] / r["threshold"]["kernel_ms_avg"]
                                                   if "threshold" in r else None),
@@ -964,6 +965,9 @@ def main_path(args, w, head, pool, n_pool, sp):
                                          "stream_sweep_kernel + scan_sweep_kernel + move_sweep_kernel")
                                         + " over three segments (one pass with the local error, event-timed together)"
                                         if args.local_error else
+                                        "one_pass_accumulate_kernel"
+                                        if args.variant != "staged" and not args.separate_scan
+                                        and w.n_total // w.world <= 1 << 22 and w.n_total <= 1 << 26 else
                                         "accumulate_kernel + stream_scan_kernel + move_kernel "
                                         "(one pass, event-timed together)" if r["fused"] else
                                         "accumulate_kernel + stream_kernel + scan_kernel + move_kernel "
