@@ -37,8 +37,21 @@ constexpr int kPassStream = 256;
 constexpr int kPassRow = kPassStream * 4;
 constexpr int kPassRowsSmall = 1, kPassRowsMid = 4, kPassRowsLarge = 6;
 constexpr int64_t kPassSmallMax = int64_t(1) << 19;  // one row up to this length
-constexpr int64_t kPassMidMax = int64_t(1) << 23;    // four rows up to this length, six above
+constexpr int64_t kPassMidMax = int64_t(1) << 22;    // four rows up to this length, six above
 constexpr uint32_t kGroupTiles = 512;
+// Launches of up to four rows per tile take their tiles by workgroup index:
+// they have at most kPassIndexTiles tiles, 129 to an XCD.  Each XCD dispatches
+// a launch's workgroups in index order, so the lowest unfinished tile of a
+// launch finds no room only where waiting tiles of other launches (on other
+// streams) fill its XCD: 608 of them (one wavefront and 8.3 KB of LDS each, 19
+// to a CU), 192 where they hold more than kPassCap pairs (five wavefronts), so
+// five launches at once (two of such dense tiles) cannot hold each other up.
+// Longer launches, two of which could fill each other's XCDs, draw their tiles
+// from a ticket counter: a tile waits only for tiles of running workgroups.
+constexpr uint32_t kPassIndexTiles = 1026;
+static_assert(kPassMidMax / (kPassRowsMid * kPassRow) + 2 <= kPassIndexTiles &&
+                  kPassSmallMax / (kPassRowsSmall * kPassRow) + 2 <= kPassIndexTiles,
+              "tiles taken by workgroup index");
 inline int pass_rows_for(int64_t len) {
     return len <= kPassSmallMax ? kPassRowsSmall : len <= kPassMidMax ? kPassRowsMid : kPassRowsLarge;
 }
@@ -150,6 +163,7 @@ struct LaunchArgs {
     // one-pass schedule
     uint64_t* status;                   // >= num_tiles look-back words
     uint64_t* group_status;             // >= ceil(num_tiles / kGroupTiles) look-back words
+    unsigned long long* ticket;         // 0 at launch, rearmed by the kernel (six-row tiles)
     uint8_t* host_dense;                // null, or mapped host memory, zero at launch: per tile its rows with
                                         // more than kStageCap selected values, where there are any
     // staged schedule and four-row one-pass tiles, theta_zero > theta_f: of the selected values only those

@@ -52,7 +52,7 @@
 //   residual (the local error of Sec. 2) in a fixed order.
 // One-pass schedule: a single launch; each workgroup streams one tile, ranks it,
 //   finds its output offset by look-back over the tiles before it and places
-//   its pairs itself.  For partitions (and sweeps) of up to kOnePassMax
+//   its pairs itself.  For partitions of up to kOnePassMax
 //   values, where the staged schedule's second launch and scan tail cost more
 //   than the look-back's contention, and wherever no staging memory exists.
 // accumulate_kernel: the error-feedback addition alone, for the part of the
@@ -1324,6 +1324,15 @@ __device__ __forceinline__ void pass_load(const LaunchArgs& a, PassTile<ROWS>& t
     }
 }
 
+// Draws the workgroup's ticket (one thread) and rearms the counter when the
+// last ticket of the launch is drawn: every other workgroup of the launch has
+// drawn its ticket by then.
+__device__ __forceinline__ uint32_t draw_ticket(unsigned long long* counter, uint32_t last) {
+    const uint32_t drawn = static_cast<uint32_t>(atomicAdd(counter, 1ull));
+    if (drawn == last) __hip_atomic_store(counter, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return drawn;
+}
+
 // The thread's selection bits, bit r * 4 + c for value (r, tid, c); values
 // outside [start, end) are never selected.
 template <int ROWS>
@@ -1371,11 +1380,10 @@ __device__ __forceinline__ void pass_store(const LaunchArgs& a, const PassTile<R
 // tiles before it in its group of kGroupTiles, each published by its own
 // workgroup, and the pairs of all groups before, by look-back over group
 // words; the group's last tile publishes the group's word.  Only the words
-// still missing are read again.  Every word waited for belongs to a
-// workgroup of lower index in the same launch, which publishes its tile's
-// count without waiting for anyone, and each XCD dispatches its workgroups in
-// index order, so by induction on the index every wait ends (the argument of
-// the fused launch above).
+// still missing are read again.  Every word waited for belongs to a lower
+// tile of the same launch, whose workgroup publishes its count without waiting
+// for anyone, and that workgroup runs or has room to (kPassIndexTiles), or ran
+// before this one drew its ticket: every wait ends.
 //
 // The look-back is bound by how often the same status lines are read: with
 // its offsets made up the kernel runs 2.5 us faster on 3.2M values, and one
@@ -1430,8 +1438,10 @@ __device__ __forceinline__ uint32_t pass_offset_of(const LaunchArgs& a, uint32_t
 // kernel whose tiles came from a ticket counter and whose first streaming
 // wavefront looked back, up to 2^20 values; the staged schedule above) and
 // now: 262,144 values 20.9 and 19.3 us, 600,001 23.3 and 20.0, 1,048,577 24.6
-// and 19.9, 3,194,629 29.8 and 27.4.  The allocation-free step: 41.9M values
-// 190 and 118 us, 400M 1.49 and 0.91 ms.
+// and 19.9, 3,194,629 29.8 and 27.4.  The allocation-free step (six rows,
+// tiles drawn from a ticket counter): 4.3M values 51.5 and 37.0 us, 41.9M 182 and
+// 119 us, 400M 1.42 and 0.92 ms; by workgroup index 29.0, 108 and 885 us, which
+// two such launches on two streams could not be allowed (kPassIndexTiles).
 // HINT: only the residual of values at or above theta_zero becomes +0.
 template <int ROWS, bool HINT>
 __device__ __forceinline__ void one_pass_tile(const LaunchArgs& a) {
@@ -1443,7 +1453,14 @@ __device__ __forceinline__ void one_pass_tile(const LaunchArgs& a) {
     const uint32_t tid = threadIdx.x;
     const int lane = tid & (kWaveSize - 1);
     const int wave = __builtin_amdgcn_readfirstlane(tid / kWaveSize);
-    const uint32_t tile = blockIdx.x;
+    uint32_t tile = blockIdx.x;
+    if constexpr (ROWS == kPassRowsLarge) {
+        __shared__ uint32_t s_tile;
+        if (tid == 0) s_tile = draw_ticket(a.ticket, a.num_tiles - 1);
+        __syncthreads();
+        tile = __builtin_amdgcn_readfirstlane(s_tile);
+        if (tile >= a.num_tiles) return;  // only reachable if the counter was not rearmed
+    }
     if (wave < WAVES) {
         PassTile<ROWS> t;
         t.base = a.base + static_cast<int64_t>(tile) * TILE;
@@ -1719,6 +1736,7 @@ hipError_t launch_one_pass(const LaunchArgs& args, int rows, const AccumulateArg
     if (!all_set(args.grad, args.residual, args.out_idx, args.out_val, args.count_out, args.host_count, args.status,
                  args.group_status))
         return hipErrorInvalidValue;
+    if (rows != kPassRowsLarge && args.num_tiles > kPassIndexTiles) return hipErrorInvalidValue;
     if (args.theta_zero > args.theta_f) {
         if (rows != kPassRowsMid) return hipErrorInvalidValue;
         launch_pass<kPassRowsMid, true>(args, acc, stream);
@@ -1726,7 +1744,7 @@ hipError_t launch_one_pass(const LaunchArgs& args, int rows, const AccumulateArg
         launch_pass<kPassRowsSmall, false>(args, acc, stream);
     } else if (rows == kPassRowsMid) {
         launch_pass<kPassRowsMid, false>(args, acc, stream);
-    } else if (rows == kPassRowsLarge && !acc) {
+    } else if (rows == kPassRowsLarge && !acc && args.ticket) {
         hipLaunchKernelGGL((one_pass_kernel<kPassRowsLarge, false>), dim3(args.num_tiles), dim3(kPassBlock), 0, stream,
                            args);
     } else {

@@ -15,6 +15,8 @@ namespace micro {
 //   words 0, 1                count_out: the selected count, the flagged word
 //   words 2, 3                where the kernel stores the counts it would
 //                             otherwise store into mapped host memory
+//   word kStaticTicketWord    the ticket counter (0 between launches), in a line
+//                             of its own
 //   words kStaticHeaderWords  one look-back status word per tile, for up to
 //   ...                       kStaticMaxTiles tiles of 4096 values (or more,
 //                             longer or fewer ones): a partition of up to
@@ -23,6 +25,7 @@ namespace micro {
 //   the last                  one look-back word per group of tiles
 //   kStaticMaxGroups words
 constexpr int64_t kStaticHeaderWords = 32;  // 256 bytes: the status words stay 256-byte aligned
+constexpr int64_t kStaticTicketWord = 16;
 constexpr int64_t kStaticMaxTiles = ((int64_t(1) << 31) + 2 + 4095) / 4096;
 constexpr int64_t kStaticMaxGroups = (kStaticMaxTiles + kGroupTiles - 1) / kGroupTiles;
 constexpr int64_t kStaticScratchWords = kStaticHeaderWords + kStaticMaxTiles + kStaticMaxGroups;

@@ -4,6 +4,8 @@ Every call goes through the C ABI (include/micro_sparsify.h) via the ctypes
 binding.  Indices, values, the selected count, the next threshold and the
 residual must equal the oracle's bit for bit; the tolerance is zero.
 """
+import threading
+
 import numpy as np
 import pytest
 import torch
@@ -629,3 +631,46 @@ def test_native_and_python_marshalling_agree():
     sp.close()
     with pytest.raises(RuntimeError):
         sp.step(g, r, 0, world, 0.01, 2.4, oi, ov)
+
+
+def test_long_one_pass_steps_on_two_streams_at_once():
+    """Two one-pass contexts, each with more tiles than the chip holds, stepped
+    by two threads on two streams: the oracle's bits on both, several steps in a
+    row (the ticket counters are zero again)."""
+    N, steps = 17_000_003, 4
+    note("long one-pass steps on two streams")
+    rng = np.random.default_rng(11)
+    g = [rng.standard_normal(N, dtype=np.float32) for _ in range(2)]
+    want = []
+    for x in g:
+        r, theta, out = np.zeros(N, np.float32), 2.5, []
+        for _ in range(steps):
+            idx, val, k, theta = oracle.step(x, r, 0, 1, 0.01, theta)
+            out.append((k, theta, idx, val))
+        want.append((out, r))
+    gs = [torch.from_numpy(x).to(DEV) for x in g]
+    rs = [torch.zeros(N, dtype=torch.float32, device=DEV) for _ in g]
+    torch.cuda.synchronize()
+    got = [[], []]
+
+    def work(i):
+        stream = torch.cuda.Stream()
+        with torch.cuda.stream(stream):
+            sp = micro.Sparsifier(N, device=DEV, variant=TICKET)
+            theta = 2.5
+            for _ in range(steps):
+                k, theta, idx, val = sp.step(gs[i], rs[i], 0, 1, 0.01, theta)
+                got[i].append((k, theta, idx.cpu().numpy(), val.cpu().numpy()))
+            sp.close()
+
+    threads = [threading.Thread(target=work, args=(i,)) for i in range(2)]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    for i in range(2):
+        assert len(got[i]) == steps
+        for (k, theta, idx, val), (ko, to, io, vo) in zip(got[i], want[i][0]):
+            assert (k, theta) == (ko, to), i
+            assert np.array_equal(idx, io) and first_mismatch(val, vo) < 0, i
+        assert first_mismatch(rs[i].cpu().numpy(), want[i][1]) < 0, i

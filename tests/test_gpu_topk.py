@@ -560,3 +560,21 @@ def test_hinted_select_at_its_limits(variant, listed, k_rank, k):
         topk_vs_oracle(g, res, 0, 1, (k + 0.5) / N, variant, sp=sp, hint=1.0)
         assert sp.last_topk_route() == micro.MICRO_TOPK_ROUTE_HINT_LIST
     sp.close()
+
+
+@pytest.mark.parametrize("listed", [256 * 4096, 256 * 4096 + 1, 1_500_000])
+def test_hinted_trim_of_long_lists(listed):
+    """Lists at the line past which the trim's chunks are drawn from the ticket
+    counter, and well past it; two calls in a row, so the counter is zero
+    again."""
+    N, k = 9_600_000, 1_000_000
+    rng = np.random.default_rng(listed)
+    g = rng.uniform(0.0, 0.5, N).astype(np.float32)
+    at = rng.permutation(N)[:listed]
+    g[at[:k]] = rng.uniform(1.0, 1.05, k).astype(np.float32)
+    g[at[k:]] = rng.uniform(0.9, 0.99, listed - k).astype(np.float32)
+    g *= rng.choice(np.float32([-1.0, 1.0]), N)
+    note(f"hinted trim of a long list listed={listed}")
+    sp = make(N, AUTO)
+    for _ in range(2):
+        topk_vs_oracle(g, np.zeros(N, np.float32), 0, 1, (k + 0.5) / N, AUTO, sp=sp, hint=1.0)
