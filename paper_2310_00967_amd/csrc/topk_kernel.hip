@@ -741,7 +741,7 @@ __device__ __forceinline__ uint32_t hinted_lookback(const uint64_t* status, uint
 // chunks of the same launch only, whose workgroups publish without waiting and
 // have room to run (kTopkIndexChunks) or ran before this one drew its ticket.
 // The draws of a 1,250-chunk list cost 16 us (100M values, k = 5M: a step 299 us
-// by workgroup index, 315 drawn, 377 with the trim's four launches).
+// by workgroup index, 315 drawn, 377 before the hinted select).
 __global__ __launch_bounds__(kTrimBlock) void topk_hinted_trim_kernel(TopkHinted a) {
     constexpr int ROWS = kTrimPer * kTrimWaves;
     static_assert(ROWS == kWave, "one (row, wavefront) count per lane");
