@@ -223,10 +223,10 @@ MICRO_API micro_status micro_sparsify_step(micro_ctx *ctx, const float *grad,
  * loops, harnesses that forbid hipMalloc, code that must not allocate after
  * start-up): no context, and no device or host allocation in the call.
  * It runs the one-pass schedule (MICRO_VARIANT_TICKET) with its scratch in
- * one static device array per device (4 MiB + 8.5 KB, held from the first
- * call on a device until the process ends): the count, one look-back word per
- * 4096 values of the partition and one per 512 of those, enough for any
- * partition of up to 2^31 - 1 values.
+ * one static device array per device (4 MiB + 12.3 KB, held from the first
+ * call on a device until the process ends): the count, a ticket counter, one
+ * look-back word per 4096 values of the partition and one per 512 of those, and
+ * 1026 tile claims, enough for any partition of up to 2^31 - 1 values.
  *   grad, residual, rank, world, density, theta, out_idx, out_val, k:
  *              as micro_sparsify_step, over a vector of n_total values on
  *              the current HIP device; same results bit for bit.

@@ -78,19 +78,24 @@ class MicroError(RuntimeError):
         self.status = status
 
 
+def bind(path):
+    """A built HIP library with the C ABI's signatures (never builds it)."""
+    if not os.path.exists(path):
+        raise RuntimeError(f"HIP library {path} is not built; run __graft_entry__.build() "
+                           "or python -m paper_2310_00967_amd.build")
+    lib = ctypes.CDLL(path)
+    for name, (res, args) in SIGNATURES.items():
+        fn = getattr(lib, name)
+        fn.restype = res
+        fn.argtypes = args
+    return lib
+
+
 def load():
     """Loads the built HIP library (never builds it; never falls back)."""
     global _lib
     if _lib is None:
-        if not os.path.exists(LIB_PATH):
-            raise RuntimeError(f"HIP library {LIB_PATH} is not built; run __graft_entry__.build() "
-                               "or python -m paper_2310_00967_amd.build")
-        lib = ctypes.CDLL(LIB_PATH)
-        for name, (res, args) in SIGNATURES.items():
-            fn = getattr(lib, name)
-            fn.restype = res
-            fn.argtypes = args
-        _lib = lib
+        _lib = bind(LIB_PATH)
     return _lib
 
 

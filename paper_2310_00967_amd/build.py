@@ -34,6 +34,10 @@ COMMON = ["-O3", "-std=c++17", "-fPIC", "-ffp-contract=off", "-fno-fast-math",
           "-Wall", "-Wextra", f"-I{INCLUDE}", f"-I{CSRC}"]
 DEVICE = [f"--offload-arch={ARCH}", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
           "-fhip-fp32-correctly-rounded-divide-sqrt", "-fvisibility=hidden"]
+# The library once more for the tests: every wait of the one-pass kernel gives
+# up at once, and most of its workgroups leave their tiles to the others.
+TAKEOVER_LIB = os.path.join(ROOT, "tests", "libmicro_takeover.so")
+TAKEOVER = ["-DMICRO_PASS_PATIENCE=1", "-DMICRO_PASS_ABSENT"]
 KERNEL_SOURCES = ["sparsify_kernel.hip", "union_kernel.hip", "static_scratch.hip", "topk_kernel.hip"]
 
 
@@ -56,9 +60,13 @@ def build_library(verbose=False, extra_device_flags=()):
     hobj = os.path.join(BUILD_DIR, "micro_sparsify.o")
     _run([cc, *COMMON, "-fvisibility=hidden", "-c", os.path.join(CSRC, "micro_sparsify.cpp"),
           "-o", hobj], verbose)
-    tmp = LIB + ".tmp"
-    _run([cc, f"--offload-arch={ARCH}", "-shared", "-fPIC", "-o", tmp, *kobjs, hobj], verbose)
-    os.replace(tmp, LIB)
+    obj = os.path.join(BUILD_DIR, "sparsify_kernel_takeover.o")
+    _run([cc, *COMMON, *DEVICE, *extra_device_flags, *TAKEOVER, "-x", "hip", "-c",
+          os.path.join(CSRC, KERNEL_SOURCES[0]), "-o", obj], verbose)
+    for lib, first in ((TAKEOVER_LIB, obj), (LIB, kobjs[0])):
+        tmp = lib + ".tmp"
+        _run([cc, f"--offload-arch={ARCH}", "-shared", "-fPIC", "-o", tmp, first, *kobjs[1:], hobj], verbose)
+        os.replace(tmp, lib)
     return LIB
 
 

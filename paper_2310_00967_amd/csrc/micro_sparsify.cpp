@@ -52,6 +52,7 @@ struct micro_ctx {
     // one-pass schedule: tile and group look-back words
     uint64_t* d_status = nullptr;
     uint64_t* d_group_status = nullptr;
+    uint32_t* d_claims = nullptr;            // kPassIndexTiles tile claims of the shorter launches
     unsigned long long* d_ticket = nullptr;  // of launches longer than kPassIndexTiles tiles
     int64_t group_capacity = 0;
     uint8_t* h_dense = nullptr;              // mapped pinned host memory: dense rows per tile, kDenseTiles
@@ -199,6 +200,8 @@ micro_status reset_scratch(micro_ctx* ctx) {
         e = hipMemsetAsync(ctx->d_status, 0, sizeof(uint64_t) * ctx->pass_capacity, ctx->stream);
     if (e == hipSuccess && ctx->d_group_status)
         e = hipMemsetAsync(ctx->d_group_status, 0, sizeof(uint64_t) * ctx->group_capacity, ctx->stream);
+    if (e == hipSuccess && ctx->d_claims)
+        e = hipMemsetAsync(ctx->d_claims, 0, sizeof(uint32_t) * micro::kPassIndexTiles, ctx->stream);
     if (e == hipSuccess && ctx->d_ticket)
         e = hipMemsetAsync(ctx->d_ticket, 0, sizeof(unsigned long long), ctx->stream);
     if (e == hipSuccess && ctx->d_chunk_status)
@@ -227,7 +230,7 @@ void release(micro_ctx* ctx) {
         if (ev) (void)hipEventDestroy(ev);
     void* device_buffers[] = {ctx->d_tile_counts, ctx->d_tile_excl, ctx->d_flagged_list, ctx->d_split_tile, ctx->d_tile_sumsq, ctx->d_stage,
                               ctx->d_chunk_status, ctx->d_tile_words, ctx->d_status, ctx->d_group_status,
-                              ctx->d_ticket, ctx->d_count, ctx->d_topk, ctx->d_hinted, ctx->d_hinted_status};
+                              ctx->d_claims, ctx->d_ticket, ctx->d_count, ctx->d_topk, ctx->d_hinted, ctx->d_hinted_status};
     for (void* p : device_buffers)
         if (p) (void)hipFree(p);
     if (ctx->h_count) (void)hipHostFree(ctx->h_count);
@@ -856,6 +859,7 @@ micro_status execute_step(micro_ctx* ctx, const float* grad, float* residual, in
     a.chunk_status = ctx->d_chunk_status;
     a.status = ctx->d_status;
     a.group_status = ctx->d_group_status;
+    a.claims = ctx->d_claims;
     a.ticket = ctx->d_ticket;
     // above kAutoTicketMax the one launch reports what the staged one would
     const bool counts_dense = !staged && reports_staged && ctx->h_dense && tiles <= kDenseTiles;
@@ -1309,6 +1313,7 @@ micro_status micro_sparsify_step_noalloc(const float* grad, float* residual, int
     a.host_count = reinterpret_cast<int64_t*>(dv.words + 2);
     a.status = dv.words + micro::kStaticHeaderWords;
     a.group_status = a.status + micro::kStaticMaxTiles;
+    a.claims = reinterpret_cast<uint32_t*>(a.group_status + micro::kStaticMaxGroups);
     a.ticket = reinterpret_cast<unsigned long long*>(dv.words + micro::kStaticTicketWord);
     a.epoch = dv.epoch + 1;
     if ((e = micro::launch_one_pass(a, rows, nullptr, stream)) != hipSuccess) return noalloc_fail(dv, e, "sparsify kernel launch");
@@ -1458,6 +1463,7 @@ micro_status micro_sparsify_init(micro_ctx** out, int64_t n_total, void* hip_str
         ctx->group_capacity = ctx->pass_capacity / micro::kGroupTiles + 1;
         ok = hipMalloc(&ctx->d_status, sizeof(uint64_t) * ctx->pass_capacity) == hipSuccess &&
              hipMalloc(&ctx->d_group_status, sizeof(uint64_t) * ctx->group_capacity) == hipSuccess &&
+             hipMalloc(&ctx->d_claims, sizeof(uint32_t) * micro::kPassIndexTiles) == hipSuccess &&
              hipMalloc(&ctx->d_ticket, sizeof(unsigned long long)) == hipSuccess;
         if (ok && ctx->has_staged)
             ok = hipHostMalloc(&ctx->h_dense, kDenseTiles, hipHostMallocMapped | hipHostMallocCoherent) ==

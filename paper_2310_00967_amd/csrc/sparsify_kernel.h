@@ -39,15 +39,14 @@ constexpr int kPassRowsSmall = 1, kPassRowsMid = 4, kPassRowsLarge = 6;
 constexpr int64_t kPassSmallMax = int64_t(1) << 19;  // one row up to this length
 constexpr int64_t kPassMidMax = int64_t(1) << 22;    // four rows up to this length, six above
 constexpr uint32_t kGroupTiles = 512;
-// Launches of up to four rows per tile take their tiles by workgroup index:
-// they have at most kPassIndexTiles tiles, 129 to an XCD.  Each XCD dispatches
-// a launch's workgroups in index order, so the lowest unfinished tile of a
-// launch finds no room only where waiting tiles of other launches (on other
-// streams) fill its XCD: 608 of them (one wavefront and 8.3 KB of LDS each, 19
-// to a CU), 192 where they hold more than kPassCap pairs (five wavefronts), so
-// five launches at once (two of such dense tiles) cannot hold each other up.
-// Longer launches, two of which could fill each other's XCDs, draw their tiles
-// from a ticket counter: a tile waits only for tiles of running workgroups.
+// Launches of up to four rows per tile, of at most kPassIndexTiles tiles, take
+// their tiles by workgroup index; a tile is processed by whoever claims it
+// first, its own workgroup or, when that has not been dispatched, one that
+// waits for it (take_over_below), so no launch needs room on the chip beside
+// others to finish.  Longer launches draw their tiles from a ticket counter: a
+// tile waits only for tiles of running workgroups.  The claims are one word a
+// tile, drawn while the tile's loads are in flight; the draws of a ticket all
+// meet at one word, before the loads.
 constexpr uint32_t kPassIndexTiles = 1026;
 static_assert(kPassMidMax / (kPassRowsMid * kPassRow) + 2 <= kPassIndexTiles &&
                   kPassSmallMax / (kPassRowsSmall * kPassRow) + 2 <= kPassIndexTiles,
@@ -163,6 +162,8 @@ struct LaunchArgs {
     // one-pass schedule
     uint64_t* status;                   // >= num_tiles look-back words
     uint64_t* group_status;             // >= ceil(num_tiles / kGroupTiles) look-back words
+    uint32_t* claims;                   // >= num_tiles words: the epoch of the last launch whose tile was
+                                        // claimed (tiles taken by workgroup index)
     unsigned long long* ticket;         // 0 at launch, rearmed by the kernel (six-row tiles)
     uint8_t* host_dense;                // null, or mapped host memory, zero at launch: per tile its rows with
                                         // more than kStageCap selected values, where there are any

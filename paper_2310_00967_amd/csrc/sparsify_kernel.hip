@@ -148,8 +148,11 @@ __device__ __forceinline__ void store_status(uint64_t* p, uint64_t v) {
 // items (groups of tiles) before `item`: sums their counts back to the nearest
 // inclusive prefix and returns the exclusive prefix (uniform).  Every word
 // before `item` is published without waiting for `item` or a later one, so
-// the retries end.
-__device__ uint32_t lookback(const uint64_t* status, uint32_t item, uint32_t epoch, int lane) {
+// the retries end; after `patience` of them (0: any number) it returns
+// kNotPublished.
+constexpr uint32_t kNotPublished = 0xffffffffu;  // no count: at most 2^31 - 1 values are selected
+__device__ __forceinline__ uint32_t lookback(const uint64_t* status, uint32_t item, uint32_t epoch, int lane,
+                                             uint32_t patience) {
     const uint64_t tag = static_cast<uint64_t>(epoch) << kEpochShift;
     uint32_t exclusive = 0;
     int64_t top = static_cast<int64_t>(item) - 1;
@@ -167,6 +170,7 @@ __device__ uint32_t lookback(const uint64_t* status, uint32_t item, uint32_t epo
         const uint64_t need = inc_mask ? (inc_mask ^ (inc_mask - 1)) : ~0ull;
         if (bad_mask & need) {
             __builtin_amdgcn_s_sleep(1);
+            if (patience != 0 && --patience == 0) return kNotPublished;
             continue;
         }
         const uint32_t v = ((need >> lane) & 1ull) ? static_cast<uint32_t>(w & kCountMask) : 0u;
@@ -1276,7 +1280,7 @@ constexpr uint32_t kPassCap = 1024;                  // pairs a tile stages in L
 // (row, thread, c) sits at base + row * kPassRow + thread * 4 + c, which is
 // also its output order.  Addresses are a uniform base plus a 32-bit offset
 // per thread: 64-bit addresses per value took the four-row kernel to 91
-// vector registers, this form needs 58.
+// vector registers, this form needs 51 (56 with the second bound).
 template <int ROWS>
 struct PassTile {
     int64_t base;      // global index of the tile's first value (uniform)
@@ -1380,10 +1384,10 @@ __device__ __forceinline__ void pass_store(const LaunchArgs& a, const PassTile<R
 // tiles before it in its group of kGroupTiles, each published by its own
 // workgroup, and the pairs of all groups before, by look-back over group
 // words; the group's last tile publishes the group's word.  Only the words
-// still missing are read again.  Every word waited for belongs to a lower
-// tile of the same launch, whose workgroup publishes its count without waiting
-// for anyone, and that workgroup runs or has room to (kPassIndexTiles), or ran
-// before this one drew its ticket: every wait ends.
+// still missing are read again, `patience` times (0: any number), then it
+// returns kNotPublished.  A wait for a lower tile of the same launch ends once
+// that tile is claimed (or drawn): its claimer publishes the count without
+// waiting for anyone, and a group's word once the lower tiles' waits have ended.
 //
 // The look-back is bound by how often the same status lines are read: with
 // its offsets made up the kernel runs 2.5 us faster on 3.2M values, and one
@@ -1392,7 +1396,8 @@ __device__ __forceinline__ void pass_store(const LaunchArgs& a, const PassTile<R
 // 45.7 us (more, smaller groups put more readers on the few group words);
 // 16-bit words, 64 to a line: 62 us; a chain of group prefixes, each in 16
 // copies, instead of the group look-back: 53 us.
-__device__ __forceinline__ uint32_t pass_offset_of(const LaunchArgs& a, uint32_t tile, uint32_t count, int lane) {
+__device__ __forceinline__ uint32_t pass_offset_of(const LaunchArgs& a, uint32_t tile, uint32_t count, int lane,
+                                                   uint32_t patience) {
     constexpr int PER = kGroupTiles / kWaveSize;
     const uint64_t tag = static_cast<uint64_t>(a.epoch) << kEpochShift;
     const uint32_t group = tile / kGroupTiles;
@@ -1415,15 +1420,135 @@ __device__ __forceinline__ uint32_t pass_offset_of(const LaunchArgs& a, uint32_t
         }
         if (__ballot(pending != 0) == 0) break;
         __builtin_amdgcn_s_sleep(4);
+        if (patience != 0 && --patience == 0) return kNotPublished;
     }
     const uint32_t in_group = wave_sum(sum);
     const bool publishes = mine == kGroupTiles - 1 && lane == 0;
     if (publishes)
         store_status(&a.group_status[group], tag | (group == 0 ? kFlagInclusive : kFlagAggregate) | (in_group + count));
     if (group == 0) return in_group;
-    const uint32_t before = lookback(a.group_status, group, a.epoch, lane);
+    const uint32_t before = lookback(a.group_status, group, a.epoch, lane, patience);
+    if (before == kNotPublished) return before;
     if (publishes) store_status(&a.group_status[group], tag | kFlagInclusive | (before + in_group + count));
     return before + in_group;
+}
+
+__device__ __forceinline__ void publish_pass_tile(const LaunchArgs& a, uint32_t tile, uint32_t count) {
+    store_status(&a.status[tile], (static_cast<uint64_t>(a.epoch) << kEpochShift) | kFlagAggregate | count);
+}
+
+// The last tile's offset and count: the launch's total (one lane).
+__device__ __forceinline__ void publish_pass_total(const LaunchArgs& a, uint32_t excl, uint32_t count) {
+    a.count_out[0] = static_cast<int64_t>(excl) + count;
+    a.host_count[0] = static_cast<int64_t>(excl) + count;
+    a.host_count[1] = 0;
+}
+
+// Claims a tile for this launch (one lane): true for the first to ask.
+__device__ __forceinline__ bool claim_tile(const LaunchArgs& a, uint32_t tile) {
+    return __hip_atomic_exchange(&a.claims[tile], a.epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != a.epoch;
+}
+
+// A tile that this wavefront has claimed, from its loads to its pairs, with
+// few registers rather than fast (64 values at a time, and twice: for the
+// count, which must be published before any wait, then for the pairs and the
+// residual).  Its offset is the sum of the counts of all tiles before it.
+template <int ROWS, bool HINT>
+__device__ __forceinline__ void place_tile_alone(const LaunchArgs& a, uint32_t tile, int lane) {
+    const int64_t base = a.base + static_cast<int64_t>(tile) * (ROWS * kPassRow);
+    const float* grad = a.grad + base;
+    float* residual = a.residual + base;
+    const int32_t lo = base < a.start ? static_cast<int32_t>(a.start - base) : 0;
+    const int32_t hi =
+        base + ROWS * kPassRow > a.end ? static_cast<int32_t>(a.end - base) : static_cast<int32_t>(ROWS * kPassRow);
+    uint32_t count = 0;
+#pragma unroll 1
+    for (int32_t j = lane; j < ROWS * kPassRow; j += kWaveSize) {  // uniform trip count
+        const bool inside = j >= lo && j < hi;
+        const float acc = inside ? grad[j] + residual[j] : 0.0f;
+        count += static_cast<uint32_t>(__popcll(__ballot(inside && __builtin_fabsf(acc) >= a.theta_f)));
+    }
+    if (lane == 0) publish_pass_tile(a, tile, count);
+    uint32_t before = 0;  // this lane's part
+#pragma unroll 1
+    for (uint32_t t = lane; __ballot(t < tile) != 0;) {  // uniform
+        const uint64_t w = t < tile ? load_status(&a.status[t]) : static_cast<uint64_t>(a.epoch) << kEpochShift;
+        if (__ballot((w >> kEpochShift) != a.epoch) != 0) {
+            __builtin_amdgcn_s_sleep(4);
+            continue;
+        }
+        before += static_cast<uint32_t>(w & kCountMask);
+        t += kWaveSize;
+    }
+    const uint32_t excl = wave_sum(before);
+    if (tile % kGroupTiles == kGroupTiles - 1 && lane == 0)
+        store_status(&a.group_status[tile / kGroupTiles],
+                     (static_cast<uint64_t>(a.epoch) << kEpochShift) | kFlagInclusive | (excl + count));
+    uint32_t pos = excl, row_first = excl, dense = 0;
+#pragma unroll 1
+    for (int32_t j = lane; j < ROWS * kPassRow; j += kWaveSize) {  // uniform trip count
+        const bool inside = j >= lo && j < hi;
+        const float acc = inside ? grad[j] + residual[j] : 0.0f;
+        const bool sel = inside && __builtin_fabsf(acc) >= a.theta_f;
+        const uint64_t mask = __ballot(sel);
+        if (sel) {
+            const uint32_t to = pos + lanes_below(mask);
+            a.out_idx[to] = static_cast<int32_t>(static_cast<uint32_t>(base) + j);
+            a.out_val[to] = acc;
+        }
+        if (inside) residual[j] = (HINT ? __builtin_fabsf(acc) >= a.theta_zero : sel) ? 0.0f : acc;
+        pos += static_cast<uint32_t>(__popcll(mask));
+        if ((j & (kPassRow - 1)) == kPassRow - kWaveSize + lane) {  // the row's last values (uniform)
+            dense += pos - row_first > kStageCap;
+            row_first = pos;
+        }
+    }
+    if (lane != 0) return;
+    if (a.host_dense && dense) a.host_dense[tile] = static_cast<uint8_t>(dense);
+    if (tile == a.num_tiles - 1) publish_pass_total(a, excl, count);
+}
+
+// Claims and processes every tile below `tile` that nobody has claimed, the
+// lowest first (one wavefront, no barriers).  Afterwards every wait of `tile`
+// is for claimed tiles, whose claimers run; so are the waits of the tiles
+// processed here, which are lower still.  By induction on the tile, every wait
+// of the launch ends, wherever and in whatever order its workgroups are
+// dispatched, also while other launches' waiting tiles fill the chip.
+template <int ROWS, bool HINT>
+__device__ __forceinline__ void take_over_below(const LaunchArgs& a, uint32_t tile, int lane) {
+    for (uint32_t first = 0; first < tile;) {
+        const uint32_t t = first + lane;
+        const bool open = t < tile && __hip_atomic_load(&a.claims[t], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) !=
+                                          a.epoch;
+        const uint64_t mask = __ballot(open);
+        if (mask == 0) {
+            first += kWaveSize;
+            continue;
+        }
+        const uint32_t lowest = first + static_cast<uint32_t>(__builtin_ctzll(mask));
+        const bool won = lane == 0 && claim_tile(a, lowest);
+        if (__ballot(won) != 0) place_tile_alone<ROWS, HINT>(a, lowest, lane);
+    }
+}
+
+// Polls of missing words after which a waiting wavefront looks for tiles to
+// take over: about 0.2 ms, several times what a launch with the chip to itself
+// takes, since a tile takes one wavefront several times as long as five.
+#ifndef MICRO_PASS_PATIENCE
+#define MICRO_PASS_PATIENCE 128
+#endif
+constexpr uint32_t kPassPatience = MICRO_PASS_PATIENCE;
+
+// The tests build the library once more with workgroups that leave without a
+// look at their tile (all but every third and the last), as if they had not
+// been dispatched: the others take those tiles over.
+__device__ __forceinline__ bool absent(const LaunchArgs& a, uint32_t tile) {
+#ifdef MICRO_PASS_ABSENT
+    return tile % 3 != 2 && tile + 1 != a.num_tiles;
+#else
+    (void)a, (void)tile;
+    return false;
+#endif
 }
 
 // One tile per workgroup: four wavefronts stream it, a fifth, which holds no
@@ -1440,8 +1565,13 @@ __device__ __forceinline__ uint32_t pass_offset_of(const LaunchArgs& a, uint32_t
 // now: 262,144 values 20.9 and 19.3 us, 600,001 23.3 and 20.0, 1,048,577 24.6
 // and 19.9, 3,194,629 29.8 and 27.4.  The allocation-free step (six rows,
 // tiles drawn from a ticket counter): 4.3M values 51.5 and 37.0 us, 41.9M 182 and
-// 119 us, 400M 1.42 and 0.92 ms; by workgroup index 29.0, 108 and 885 us, which
-// two such launches on two streams could not be allowed (kPassIndexTiles).
+// 119 us, 400M 1.42 and 0.92 ms.
+//
+// Tiles taken by index are claimed by the placing wavefront while the loads are
+// in flight, one word a tile: 262,144 values 16.25 us against 16.4 without
+// claims, ResNet-50 rank 0 24.4 against 24.2, ResNet-18's allocation-free step
+// 20.5 against 20.2; with their tiles drawn from one ticket counter before the
+// loads 19.0, 34.6 and 22.5 us.
 // HINT: only the residual of values at or above theta_zero becomes +0.
 template <int ROWS, bool HINT>
 __device__ __forceinline__ void one_pass_tile(const LaunchArgs& a) {
@@ -1453,8 +1583,12 @@ __device__ __forceinline__ void one_pass_tile(const LaunchArgs& a) {
     const uint32_t tid = threadIdx.x;
     const int lane = tid & (kWaveSize - 1);
     const int wave = __builtin_amdgcn_readfirstlane(tid / kWaveSize);
+    __shared__ uint32_t s_claimed;
+    constexpr bool CLAIMED = ROWS != kPassRowsLarge;
     uint32_t tile = blockIdx.x;
-    if constexpr (ROWS == kPassRowsLarge) {
+    if constexpr (CLAIMED) {
+        if (absent(a, tile)) return;
+    } else {
         __shared__ uint32_t s_tile;
         if (tid == 0) s_tile = draw_ticket(a.ticket, a.num_tiles - 1);
         __syncthreads();
@@ -1472,6 +1606,7 @@ __device__ __forceinline__ void one_pass_tile(const LaunchArgs& a) {
         uint32_t lane_rank[ROWS], row_count[ROWS], row_base[ROWS];
         wave_ranks<4, ROWS>(sel, lane_rank, row_count);
         const uint32_t count = tile_ranks<ROWS, WAVES>(row_count, lane, wave, s_wave_total, row_base);  // barrier 1
+        if (CLAIMED && !s_claimed) return;  // uniform in the workgroup
         // the two placements share no code: what they share would be kept in
         // registers across the barriers (76 instead of 58 with four rows)
         if (count <= kPassCap) {  // uniform
@@ -1508,13 +1643,23 @@ __device__ __forceinline__ void one_pass_tile(const LaunchArgs& a) {
         }
         return;
     }
+    if (CLAIMED && lane == 0) s_claimed = claim_tile(a, tile);  // while the tile's loads are in flight
     __syncthreads();  // barrier 1
+    if (CLAIMED && !s_claimed) return;  // a waiting workgroup has taken the tile over
     const uint32_t part = lane < ROWS * WAVES ? s_wave_total[lane] : 0u;
     const uint32_t count = wave_sum(part);
-    if (lane == 0)
-        store_status(&a.status[tile], (static_cast<uint64_t>(a.epoch) << kEpochShift) | kFlagAggregate | count);
+    if (lane == 0) publish_pass_tile(a, tile, count);
     __syncthreads();  // barrier 2: the pairs are in LDS
-    const uint32_t excl = pass_offset_of(a, tile, count, lane);
+    uint32_t excl;
+    if constexpr (CLAIMED) {
+        uint32_t patience = kPassPatience;
+        while ((excl = pass_offset_of(a, tile, count, lane, patience)) == kNotPublished) {
+            take_over_below<ROWS, HINT>(a, tile, lane);
+            patience = 0;
+        }
+    } else {
+        excl = pass_offset_of(a, tile, count, lane, 0);
+    }
     if (count > kPassCap) {  // uniform
         if (lane == 0) s_exclusive = excl;
         __syncthreads();  // barrier 3
@@ -1535,11 +1680,7 @@ __device__ __forceinline__ void one_pass_tile(const LaunchArgs& a) {
         const uint64_t dense = __ballot(lane % WAVES == 0 && row > kStageCap);
         if (dense && lane == 0) a.host_dense[tile] = static_cast<uint8_t>(__popcll(dense));
     }
-    if (tile == a.num_tiles - 1 && lane == 0) {
-        a.count_out[0] = static_cast<int64_t>(excl) + count;
-        a.host_count[0] = static_cast<int64_t>(excl) + count;
-        a.host_count[1] = 0;
-    }
+    if (tile == a.num_tiles - 1 && lane == 0) publish_pass_total(a, excl, count);
 }
 
 template <int ROWS, bool HINT>
@@ -1736,7 +1877,7 @@ hipError_t launch_one_pass(const LaunchArgs& args, int rows, const AccumulateArg
     if (!all_set(args.grad, args.residual, args.out_idx, args.out_val, args.count_out, args.host_count, args.status,
                  args.group_status))
         return hipErrorInvalidValue;
-    if (rows != kPassRowsLarge && args.num_tiles > kPassIndexTiles) return hipErrorInvalidValue;
+    if (rows != kPassRowsLarge && (args.num_tiles > kPassIndexTiles || !args.claims)) return hipErrorInvalidValue;
     if (args.theta_zero > args.theta_f) {
         if (rows != kPassRowsMid) return hipErrorInvalidValue;
         launch_pass<kPassRowsMid, true>(args, acc, stream);

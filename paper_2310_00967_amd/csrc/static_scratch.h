@@ -11,7 +11,7 @@ namespace micro {
 
 // The allocation-free step runs the one-pass schedule with its scratch in one
 // static device array per device, of kStaticScratchWords 64-bit words
-// (4 MiB + 8.5 KB):
+// (4 MiB + 12.3 KB):
 //   words 0, 1                count_out: the selected count, the flagged word
 //   words 2, 3                where the kernel stores the counts it would
 //                             otherwise store into mapped host memory
@@ -22,13 +22,16 @@ namespace micro {
 //                             longer or fewer ones): a partition of up to
 //                             2^31 - 1 values (the int32 index range) plus the
 //                             16-byte alignment of its first tile
-//   the last                  one look-back word per group of tiles
+//   the next                  one look-back word per group of tiles
 //   kStaticMaxGroups words
+//   the last                  one 32-bit claim per tile of a launch that takes its
+//   kStaticClaimWords words   tiles by workgroup index
 constexpr int64_t kStaticHeaderWords = 32;  // 256 bytes: the status words stay 256-byte aligned
 constexpr int64_t kStaticTicketWord = 16;
 constexpr int64_t kStaticMaxTiles = ((int64_t(1) << 31) + 2 + 4095) / 4096;
 constexpr int64_t kStaticMaxGroups = (kStaticMaxTiles + kGroupTiles - 1) / kGroupTiles;
-constexpr int64_t kStaticScratchWords = kStaticHeaderWords + kStaticMaxTiles + kStaticMaxGroups;
+constexpr int64_t kStaticClaimWords = (kPassIndexTiles + 1) / 2;
+constexpr int64_t kStaticScratchWords = kStaticHeaderWords + kStaticMaxTiles + kStaticMaxGroups + kStaticClaimWords;
 
 // The device address of the static scratch on the current device, looked up
 // once per device with hipGetSymbolAddress and kept.  Thread-safe.
