@@ -131,13 +131,6 @@ constexpr int kTopkHintedGroups = kTopkHintedFine + kTopkFine;
 constexpr int kTopkHintedState = kTopkHintedGroups + kTopkGroups * kTopkGroupStride;
 constexpr int kTopkHintedTicket = kTopkHintedState + 32;  // launch 3's ticket counter (0 between launches), its own line
 constexpr int kTopkHintedWords = kTopkHintedTicket + 32;
-// Longest list, in chunks, whose chunks launch 3 takes by workgroup index: 32
-// to an XCD, which holds 160 of its workgroups, so five such launches at once
-// (on several streams) cannot fill an XCD that another's lowest unfinished
-// chunk waits for.  The chunks of longer lists are drawn from the ticket
-// counter in increasing order: a chunk waits only for chunks of running
-// workgroups.
-constexpr uint32_t kTopkIndexChunks = 256;
 constexpr int kTopkKeysBlock = 1024;
 static_assert(kTopkWindowBins + 1 <= kTopkHintedFine, "the bins end before the key counters");
 

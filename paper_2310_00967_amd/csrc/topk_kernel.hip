@@ -737,11 +737,12 @@ __device__ __forceinline__ uint32_t hinted_lookback(const uint64_t* status, uint
 // its counts are published (the wait and the barrier below), and a chunk
 // stores only once the counts of every chunk before it are published, to
 // positions no later than its own entries': so no store reaches an entry that
-// has not been read, and the list is compacted in place.  Waits are for lower
-// chunks of the same launch only, whose workgroups publish without waiting and
-// have room to run (kTopkIndexChunks) or ran before this one drew its ticket.
-// The draws of a 1,250-chunk list cost 16 us (100M values, k = 5M: a step 299 us
-// by workgroup index, 315 drawn, 377 before the hinted select).
+// has not been read, and the list is compacted in place.  Chunks are drawn from
+// a ticket counter: waits are for lower chunks of the same launch only, whose
+// workgroups drew theirs before and publish without waiting, whatever other
+// launches hold the chip.  The draws cost BERT-large's 200 chunks 0.5 us (a
+// step 124.5 us by workgroup index, 125.0 drawn) and 1,250 chunks 16 us (100M
+// values, k = 5M: 299 and 315 us, 377 before the hinted select).
 __global__ __launch_bounds__(kTrimBlock) void topk_hinted_trim_kernel(TopkHinted a) {
     constexpr int ROWS = kTrimPer * kTrimWaves;
     static_assert(ROWS == kWave, "one (row, wavefront) count per lane");
@@ -758,20 +759,17 @@ __global__ __launch_bounds__(kTrimBlock) void topk_hinted_trim_kernel(TopkHinted
         for (int b = tid; b < kTopkWindowBins + 1; b += kTrimBlock) a.words[kTopkHintedBins + b] = 0u;
         if (!ok && tid == 0) a.host[5] = 4;
     }
-    uint32_t chunk = blockIdx.x;
-    if (!ok || static_cast<int64_t>(chunk) * kTopkTrimChunk >= n) return;  // uniform
+    if (!ok || static_cast<int64_t>(blockIdx.x) * kTopkTrimChunk >= n) return;  // uniform
     const uint32_t chunks = static_cast<uint32_t>((n + kTopkTrimChunk - 1) / kTopkTrimChunk);
-    if (chunks > kTopkIndexChunks) {  // uniform
-        if (tid == 0) {
-            const uint32_t drawn = atomicAdd(&a.words[kTopkHintedTicket], 1u);
-            if (drawn == chunks - 1)  // every other workgroup has drawn its ticket
-                __hip_atomic_store(&a.words[kTopkHintedTicket], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            s_item = drawn;
-        }
-        __syncthreads();
-        chunk = __builtin_amdgcn_readfirstlane(s_item);
-        if (chunk >= chunks) return;  // only reachable if the counter was not rearmed
+    if (tid == 0) {
+        const uint32_t drawn = atomicAdd(&a.words[kTopkHintedTicket], 1u);
+        if (drawn == chunks - 1)  // every other workgroup has drawn its ticket
+            __hip_atomic_store(&a.words[kTopkHintedTicket], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        s_item = drawn;
     }
+    __syncthreads();
+    const uint32_t chunk = __builtin_amdgcn_readfirstlane(s_item);
+    if (chunk >= chunks) return;  // only reachable if the counter was not rearmed
     const int64_t base = static_cast<int64_t>(chunk) * kTopkTrimChunk;
     float val[kTrimPer];
     int32_t idx[kTrimPer];

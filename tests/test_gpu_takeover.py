@@ -1,11 +1,11 @@
-"""Launches that take their tiles by workgroup index, where not every workgroup
-is there when its tile is waited for (GPU).
+"""Launches whose workgroups wait for lower tiles or chunks, where not every
+workgroup is there when it is waited for (GPU).
 
 The chip may be filled by other launches' waiting tiles while a launch's lower
 tiles have not been dispatched, so a tile that is waited for and that nobody
 has claimed is processed by the workgroup that waits.  The first test runs the
 library built so that every wait gives up at once and two of three workgroups
-leave without a look at their tile; the second runs many such launches at once.
+leave without a look at their tile; the others run many such launches at once.
 The oracle's bits each time.
 """
 import os
@@ -104,6 +104,20 @@ def test_tiles_of_absent_workgroups_are_taken_over(takeover, length, offset, ent
         sp.close()
 
 
+def on_streams(threads, work):
+    """work(i) in a thread and on a stream of its own, for each i."""
+    def run(i):
+        with torch.cuda.stream(torch.cuda.Stream()):
+            work(i)
+
+    torch.cuda.synchronize()
+    pool = [threading.Thread(target=run, args=(i,)) for i in range(threads)]
+    for t in pool:
+        t.start()
+    for t in pool:
+        t.join()
+
+
 @pytest.mark.parametrize("theta", [2.5, 0.7])  # 0.7: tiles with more pairs than they stage, five wavefronts each
 def test_steps_on_many_streams_at_once(theta):
     """Eight contexts stepped by eight threads on streams of their own, each a
@@ -112,30 +126,54 @@ def test_steps_on_many_streams_at_once(theta):
     note(f"one-launch steps on many streams theta={theta}")
     rng = np.random.default_rng(3)
     g = rng.standard_normal(N, dtype=np.float32)
-    res, th, want = np.zeros(N, np.float32), theta, []
+    res, want = np.zeros(N, np.float32), []
     for _ in range(steps):
-        idx, val, k, _ = oracle.step(g, res, 0, 1, 0.01, th)
+        idx, val, k, _ = oracle.step(g, res, 0, 1, 0.01, theta)
         want.append((k, idx, val))
     g_dev = torch.from_numpy(g).to(DEV)
     out = [torch.zeros(N, dtype=torch.float32, device=DEV) for _ in range(threads)]
-    torch.cuda.synchronize()
     got = [[] for _ in range(threads)]
 
     def work(i):
-        with torch.cuda.stream(torch.cuda.Stream()):
-            sp = micro.Sparsifier(N, device=DEV)
-            for _ in range(steps):
-                k, _, idx, val = sp.step(g_dev, out[i], 0, 1, 0.01, theta)
-                got[i].append((k, idx.cpu().numpy(), val.cpu().numpy()))
-            sp.close()
+        sp = micro.Sparsifier(N, device=DEV)
+        for _ in range(steps):
+            k, _, idx, val = sp.step(g_dev, out[i], 0, 1, 0.01, theta)
+            got[i].append((k, idx.cpu().numpy(), val.cpu().numpy()))
+        sp.close()
 
-    pool = [threading.Thread(target=work, args=(i,)) for i in range(threads)]
-    for t in pool:
-        t.start()
-    for t in pool:
-        t.join()
+    on_streams(threads, work)
     for i in range(threads):
         assert len(got[i]) == steps, i
         for (k, idx, val), (ko, io, vo) in zip(got[i], want):
             assert k == ko and np.array_equal(idx, io) and first_mismatch(val, vo) < 0, i
+        assert first_mismatch(out[i].cpu().numpy(), res) < 0, i
+
+
+def test_hinted_trims_on_many_streams_at_once():
+    """Eight top-k contexts likewise, lists of about 150 of the trim's chunks."""
+    N, steps, threads, density = 4_500_000, 4, 8, 0.12
+    note("hinted trims on many streams")
+    rng = np.random.default_rng(4)
+    g = rng.standard_normal(N, dtype=np.float32)
+    res, want, hint = np.zeros(N, np.float32), [], []
+    for _ in range(steps):
+        hint.append(oracle.topk_step(g, res.copy(), 0, 1, density, 1.0)[3])
+        idx, val, k, th = oracle.topk_step(g, res, 0, 1, density, hint[-1])
+        want.append((k, th, idx, val))
+    g_dev = torch.from_numpy(g).to(DEV)
+    out = [torch.zeros(N, dtype=torch.float32, device=DEV) for _ in range(threads)]
+    got = [[] for _ in range(threads)]
+
+    def work(i):
+        sp = micro.Sparsifier(N, device=DEV, rule=micro.MICRO_RULE_TOPK)
+        for t in range(steps):
+            k, th, idx, val = sp.step(g_dev, out[i], 0, 1, density, hint[t])
+            got[i].append((k, th, idx.cpu().numpy(), val.cpu().numpy()))
+        sp.close()
+
+    on_streams(threads, work)
+    for i in range(threads):
+        assert len(got[i]) == steps, i
+        for (k, th, idx, val), (ko, to, io, vo) in zip(got[i], want):
+            assert (k, th) == (ko, to) and np.array_equal(idx, io) and first_mismatch(val, vo) < 0, i
         assert first_mismatch(out[i].cpu().numpy(), res) < 0, i

@@ -564,9 +564,8 @@ def test_hinted_select_at_its_limits(variant, listed, k_rank, k):
 
 @pytest.mark.parametrize("listed", [256 * 4096, 256 * 4096 + 1, 1_500_000])
 def test_hinted_trim_of_long_lists(listed):
-    """Lists at the line past which the trim's chunks are drawn from the ticket
-    counter, and well past it; two calls in a row, so the counter is zero
-    again."""
+    """Lists of 256, 257 and 367 of the trim's chunks; two calls in a row, so the
+    ticket counter is zero again."""
     N, k = 9_600_000, 1_000_000
     rng = np.random.default_rng(listed)
     g = rng.uniform(0.0, 0.5, N).astype(np.float32)
