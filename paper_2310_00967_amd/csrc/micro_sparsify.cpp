@@ -23,10 +23,22 @@
 
 // The top-k comparator's step under a hint looks from (1 - slack) times the
 // hint up.  The slack follows how far the k-th magnitude was from the hint in
-// the context's last hinted steps, from kTopkSlackMax (where it starts, and
-// where a list that held fewer than k values puts it back) down to
-// kTopkSlackMin; the result never depends on it.
-constexpr double kTopkSlackMax = 0.125, kTopkSlackMin = 1.0 / 512.0;
+// the context's last hinted steps, from kTopkSlackMax (where it starts) down by
+// a fifth per step to kTopkSlackQuick and from there by a fiftieth to
+// kTopkSlackMin; the result never depends on it.  A k-th magnitude further
+// below the hint than that makes the step's list fall short, and the select
+// starts over on the residual.  Time of a step on BERT-large rank 3 and
+// ResNet-50 rank 0 (d = 0.01 and 0.001) at a fixed slack of 1/8: 148 and 62 us;
+// settled at a least slack of 1/16 137 and 58, 1/32 124-137 and 36-57, 1/64
+// 124-128 and 35-60, 1/512 123 and 33-37 (the upper figures after hundreds of steps
+// on one gradient, which fill up the magnitudes next to the k-th); one that
+// falls short 325 and 125.  So 1/64 has most of the gain and takes a sudden fall
+// of 1.5%, and it takes about a hundred steps that moved by less than 0.1% to come
+// to the least: a list that falls short there is paid for by the steps before.
+// After a step that fell short where 1/8 would have served the slack stays at
+// its most for kTopkSlackHold steps.
+constexpr double kTopkSlackMax = 0.125, kTopkSlackQuick = 1.0 / 64.0, kTopkSlackMin = 1.0 / 512.0;
+constexpr int kTopkSlackHold = 16;
 
 struct micro_ctx {
     int device = -1;
@@ -67,6 +79,7 @@ struct micro_ctx {
     uint32_t* d_topk = nullptr;              // kTopkBins counters (zero between passes), kTopkStateWords
     // how far below the hint the next hinted step looks (its share of the hint)
     double topk_slack = kTopkSlackMax;
+    int topk_slack_hold = 0;                 // steps for which the slack stays at its most
     uint32_t* d_hinted = nullptr;            // MICRO_RULE_TOPK: the hinted select's counters, kTopkHintedWords
     uint64_t* d_hinted_status = nullptr;     // and its look-back words
     int64_t hinted_chunks = 0;               // list chunks they hold (two words each)
@@ -916,6 +929,7 @@ micro_status execute_step(micro_ctx* ctx, const float* grad, float* residual, in
     // the step's count calls for; else the list route's last passes over the
     // step's output list, and the trim to the top k.
     bool finished = false;  // nothing left to enqueue or to wait for
+    bool fell_short = false;  // the list, under a bound closer than the slack's most
     if (topk && plan.route == TopkRoute::kHint) {
         // The hinted select and the trim read the list's length on the
         // device, so they follow the step without a wait; where they report
@@ -968,10 +982,22 @@ micro_status execute_step(micro_ctx* ctx, const float* grad, float* residual, in
             // down, now or (fading) in the last steps
             const double moved =
                 std::fabs(1.0 - static_cast<double>(float_from_bits(static_cast<uint32_t>(h[0]))) / *theta);
-            ctx->topk_slack = std::min(kTopkSlackMax, std::max({kTopkSlackMin, 3.0 * moved, 0.8 * ctx->topk_slack}));
+            if (ctx->topk_slack_hold > 0) {
+                --ctx->topk_slack_hold;
+                ctx->topk_slack = kTopkSlackMax;
+            } else {
+                const double faded = ctx->topk_slack > kTopkSlackQuick ? std::max(kTopkSlackQuick, 0.8 * ctx->topk_slack)
+                                                                       : 0.98 * ctx->topk_slack;
+                ctx->topk_slack = std::min(kTopkSlackMax, std::max({kTopkSlackMin, 3.0 * moved, faded}));
+            }
         } else {
-            // too few listed, or too many
-            ctx->topk_slack = listed < want ? kTopkSlackMax : std::max(kTopkSlackMin, 0.5 * ctx->topk_slack);
+            if (listed > hs.max_list) {
+                ctx->topk_slack = std::max(kTopkSlackMin, 0.5 * ctx->topk_slack);
+                ctx->topk_slack_hold = 0;
+            } else {  // too few listed, or the k-th magnitude far above the hint
+                fell_short = listed < want && ctx->topk_slack < kTopkSlackMax;
+                ctx->topk_slack = kTopkSlackMax;
+            }
             const micro_status s = topk_after_hint(ctx, &plan, listed, residual, start, len, density, out_idx, out_val);
             if (s != MICRO_OK) return s;
         }
@@ -990,8 +1016,10 @@ micro_status execute_step(micro_ctx* ctx, const float* grad, float* residual, in
         return MICRO_EHIP;
     }
     if (topk) {
+        const double hint = *theta;
         const micro_status s = topk_finish(ctx, plan, selected, &selected, theta, nullptr);
         if (s != MICRO_OK) return s;
+        if (fell_short && selected > 0 && *theta >= hint * (1.0 - kTopkSlackMax)) ctx->topk_slack_hold = kTopkSlackHold;
     }
     if (timed && (e = hipEventElapsedTime(&ctx->stats.kernel_ms, ctx->ev[0], ctx->ev[1])) != hipSuccess)
         return hip_fail(ctx, e, "hipEventElapsedTime");

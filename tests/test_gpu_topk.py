@@ -577,3 +577,41 @@ def test_hinted_trim_of_long_lists(listed):
     sp = make(N, AUTO)
     for _ in range(2):
         topk_vs_oracle(g, np.zeros(N, np.float32), 0, 1, (k + 0.5) / N, AUTO, sp=sp, hint=1.0)
+
+
+def test_bound_of_the_hint_after_quiet_steps():
+    """Steps whose hint is the exact k-th magnitude bring the bound closer to
+    the hint.  After twenty of them a k-th magnitude 0.3%, 1% or 1.25% below the
+    hint is still found in the step's list; one 2% below it is not, and for 16
+    steps after that the bound is 7/8 of the hint again, which finds one 12%
+    below it.  After 150 it takes one 0.15% below and not one 0.3% below.
+    Exact each time."""
+    N, density = 50_003, 0.01
+    rng = np.random.default_rng(21)
+    g, res = gen(rng, N, "normal")
+    kth = oracle.topk_step(g, res.copy(), 0, 1, density, 1.0)[3]
+    LIST, PICK = micro.MICRO_TOPK_ROUTE_HINT_LIST, micro.MICRO_TOPK_ROUTE_HINT_PICK
+    note("top-k bound after quiet steps")
+
+    def route_of(fall):
+        topk_vs_oracle(g, res, 0, 1, density, sp=sp, hint=kth / (1.0 - fall))
+        return sp.last_topk_route()
+
+    for fall in (0.003, 0.01, 0.0125):
+        sp = make(N)
+        assert all(route_of(0.0) == LIST for _ in range(20))
+        assert route_of(fall) == LIST, fall
+        sp.close()
+    sp = make(N)
+    assert all(route_of(0.0) == LIST for _ in range(20))
+    assert route_of(0.02) == PICK
+    assert all(route_of(0.0) == LIST for _ in range(15))
+    assert route_of(0.12) == LIST
+    assert route_of(0.13) == PICK  # no bound would have served: the next steps' comes closer at once
+    assert all(route_of(0.0) == LIST for _ in range(20))
+    assert route_of(0.02) == PICK
+    assert all(route_of(0.0) == LIST for _ in range(16 + 150))
+    assert route_of(0.0015) == LIST
+    assert all(route_of(0.0) == LIST for _ in range(60))
+    assert route_of(0.003) == PICK
+    sp.close()
