@@ -284,6 +284,7 @@ def measure(w, density, pool, sp, micro, warmup, steps, cycle=False, jsonl=None)
         "ms_per_step": elapsed * 1e3 / steps,
         "variant": run.variant,
         "fused": run.fused,
+        "one_launch": sp.last_one_launch(),
     }
 
 
@@ -364,7 +365,7 @@ def measure_ef(w, density, pool, sp, warmup, steps, local_error=False):
         k, theta = out[0], out[1]
         if t >= warmup:
             log.append((N, k, sp.last_stats()[0]))
-    fused = bool(sp.last_stats()[3])
+    fused, one_launch = bool(sp.last_stats()[3]), sp.last_one_launch()
     torch.cuda.synchronize()
     elapsed = time.perf_counter() - t0
     alg = sum(12 * n + 8 * k for n, k, _ in log)
@@ -372,7 +373,8 @@ def measure_ef(w, density, pool, sp, warmup, steps, local_error=False):
     return {"g_elem_s": sum(n for n, _, _ in log) / elapsed / 1e9, "wall_gbs": alg / elapsed / 1e9,
             "kernel_gbs": alg / kernel_s / 1e9, "kernel_ms_avg": kernel_s * 1e3 / len(log),
             "alg_bytes_per_launch": alg / len(log), "ms_per_step": elapsed * 1e3 / steps,
-            "k_avg": sum(k for _, k, _ in log) / len(log), "worker": worker, "fused": fused}
+            "k_avg": sum(k for _, k, _ in log) / len(log), "worker": worker, "fused": fused,
+            "one_launch": one_launch}
 
 
 def measure_topk(w, density, pool, warmup, steps, only_topk=False, hint="last"):
@@ -965,9 +967,9 @@ def main_path(args, w, head, pool, n_pool, sp):
                                          "stream_sweep_kernel + scan_sweep_kernel + move_sweep_kernel")
                                         + " over three segments (one pass with the local error, event-timed together)"
                                         if args.local_error else
-                                        "one_pass_accumulate_kernel"
-                                        if args.variant != "staged" and not args.separate_scan
-                                        and w.n_total // w.world <= 1 << 22 and w.n_total <= 1 << 26 else
+                                        "one_pass_accumulate_kernel" if r["one_launch"] == 2 else
+                                        "accumulate_kernel + one_pass_kernel (one pass, event-timed together)"
+                                        if r["one_launch"] else
                                         "accumulate_kernel + stream_scan_kernel + move_kernel "
                                         "(one pass, event-timed together)" if r["fused"] else
                                         "accumulate_kernel + stream_kernel + scan_kernel + move_kernel "
@@ -1056,8 +1058,6 @@ def main():
                and not args.separate_scan and args.variant == "auto" else None)
     parts = sorted({ln for (_, ln) in (micro.micro_partition(w.n_total, p, w.world)
                                        for p in (range(w.world) if args.cycle else w.ranks))})
-    one_launch = (main_res["variant"] != micro.MICRO_VARIANT_STAGED
-                  or (args.variant == "auto" and not args.separate_scan and max(parts) <= 1 << 22))
     line = {
         "metric": METRIC,
         "value": main_res["g_elem_s"],
@@ -1095,7 +1095,7 @@ def main():
             "unit": "GB/s",
             "frac": main_res["kernel_gbs"] / HBM_PEAK_GBS,
             "traffic": traffic,
-            "kernel": ("one_pass_kernel" if one_launch else
+            "kernel": ("one_pass_kernel" if main_res["one_launch"] else
                        "stream_scan_kernel + move_kernel (one step, event-timed together)" if main_res["fused"] else
                        "stream_kernel + scan_kernel + move_kernel (one step, event-timed together)"),
             "kernel_ms_avg": main_res["kernel_ms_avg"],

@@ -149,19 +149,27 @@ typedef struct micro_config {
 typedef struct micro_step_stats {
     float kernel_ms;        /* device time of its kernels from HIP events
                                (MICRO_FLAG_TIME_KERNEL), else -1               */
+    int32_t one_launch;     /* 1 if its step on the partition was one launch,
+                               placing included (whichever schedule `variant`
+                               names), 2 if a full pass accumulated the rest of
+                               the vector in the same launch, else 0           */
     int64_t redone_tiles;   /* STAGED: 1024-value tiles with more selected
                                values than their staging slot holds (256),
                                redone by the placing pass instead (AUTO's
                                single launch: counted, and placed from
                                registers where four of them hold over 1024)    */
-    int32_t variant;        /* the schedule the last step ran:
-                               MICRO_VARIANT_TICKET or MICRO_VARIANT_STAGED    */
+    int32_t variant;        /* the schedule of the last step, MICRO_VARIANT_TICKET
+                               or MICRO_VARIANT_STAGED (AUTO above 2^20 values:
+                               STAGED, also where one_launch is not 0)         */
     int32_t fused;          /* 1 if its streaming and scan passes ran as one
                                launch (micro_sparsify_step, STAGED; also where
                                the placing pass was part of it), else 0        */
     int32_t topk_route;     /* MICRO_RULE_TOPK: how the step found the k-th
                                magnitude (MICRO_TOPK_ROUTE_*); 0 for the other
                                rules, or when nothing was selectable           */
+    int32_t topk_passes;    /* MICRO_RULE_TOPK: 1 if histogram passes ran; 0 where
+                               the select enqueued with a hinted step found the
+                               k-th magnitude in its list, and for other rules  */
 } micro_step_stats;
 
 /* Fills *cfg with the defaults listed above. */

@@ -285,5 +285,17 @@ class Sparsifier:
         self.last_stats()
         return self._stats_c.topk_route
 
+    def last_topk_passes(self):
+        """MICRO_RULE_TOPK: 1 if the last step ran histogram passes, 0 where the
+        select enqueued with a hinted step found the k-th magnitude."""
+        self.last_stats()
+        return self._stats_c.topk_passes
+
+    def last_one_launch(self):
+        """1 if the last step on the partition was one launch, 2 if a full pass
+        accumulated the rest of the vector in it too, else 0."""
+        self.last_stats()
+        return self._stats_c.one_launch
+
     def last_kernel_ms(self):
         return self.last_stats()[0]

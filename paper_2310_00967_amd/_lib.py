@@ -30,8 +30,9 @@ class micro_config(ctypes.Structure):
 
 
 class micro_step_stats(ctypes.Structure):
-    _fields_ = [("kernel_ms", ctypes.c_float), ("redone_tiles", ctypes.c_int64),
-                ("variant", ctypes.c_int32), ("fused", ctypes.c_int32), ("topk_route", ctypes.c_int32)]
+    _fields_ = [("kernel_ms", ctypes.c_float), ("one_launch", ctypes.c_int32), ("redone_tiles", ctypes.c_int64),
+                ("variant", ctypes.c_int32), ("fused", ctypes.c_int32), ("topk_route", ctypes.c_int32),
+                ("topk_passes", ctypes.c_int32)]
 
 
 _cfgp = ctypes.POINTER(micro_config)

@@ -787,6 +787,7 @@ micro_status execute_step(micro_ctx* ctx, const float* grad, float* residual, in
             sq[1] += returned;  // the values the trim returned to the residual
             *k = kk[1];
             ctx->stats.topk_route = topk_route_code(plan.route);
+            ctx->stats.topk_passes = len > 0 ? 1 : 0;
         } else {
             *k = kk[1];
             *theta = next_threshold(ctx->cfg, density, len, kk[1], *theta);
@@ -1026,7 +1027,9 @@ micro_status execute_step(micro_ctx* ctx, const float* grad, float* residual, in
     ctx->stats.redone_tiles = staged ? host_count[1] : counts_dense ? dense_rows(ctx, tiles) : 0;
     ctx->stats.variant = reports_staged ? MICRO_VARIANT_STAGED : MICRO_VARIANT_TICKET;
     ctx->stats.fused = len > 0 && (fused || (reports_staged && !staged)) ? 1 : 0;
+    ctx->stats.one_launch = staged || len == 0 ? 0 : acc_in_pass ? 2 : 1;
     ctx->stats.topk_route = topk ? topk_route_code(plan.route) : 0;
+    ctx->stats.topk_passes = topk && len > 0 && !finished ? 1 : 0;
     *k = selected;
     if (!topk) *theta = next_threshold(ctx->cfg, density, len, selected, *theta);
     return MICRO_OK;
@@ -1146,7 +1149,9 @@ micro_status run_segments(micro_ctx* ctx, const float* grad, float* residual, in
     ctx->stats.redone_tiles = host_count[1];
     ctx->stats.variant = MICRO_VARIANT_STAGED;
     ctx->stats.fused = fused ? 1 : 0;
+    ctx->stats.one_launch = 0;
     ctx->stats.topk_route = 0;
+    ctx->stats.topk_passes = 0;
     for (int32_t r = 0; r < count; ++r) {
         k[r] = host_count[2 + r];
         // the segment's chunks in increasing order

@@ -450,6 +450,8 @@ def test_pass_in_one_launch(N, world, shift):
             r_dev = torch.from_numpy(res0).to(DEV)
             k, th, c, idx, val = sp.ef_step(g_dev, r_dev, 0, worker, world, 0.01, theta)
             where = (N, world, worker, rule)
+            outside = N - oracle.partition(N, c, world)[1]
+            assert sp.last_one_launch() == (2 if 0 < outside <= 1 << 26 else 1), where
             assert (k, th, c) == (k_or, th_or, c_or), where
             assert np.array_equal(idx.cpu().numpy(), o_idx), where
             assert first_mismatch(val.cpu().numpy(), o_val) < 0, where

@@ -575,6 +575,7 @@ def test_one_launch_at_the_edges_of_its_tiles_groups_and_dispatch(length, offset
                 _, redone, variant, fused = sp.last_stats()
                 staged = entry == "auto" and N > 1 << 20
                 assert (variant, fused) == ((STAGED, 1) if staged else (TICKET, 0)), where
+                assert sp.last_one_launch() == (0 if entry == "auto" and N > 1 << 22 else 1), where
                 assert (redone > 0) == staged, where
                 sp.close()
             torch.cuda.synchronize()

@@ -547,7 +547,7 @@ def test_hinted_select_at_its_limits(variant, listed, k_rank, k):
         top[:] = np.float32(1.03)       # k + listed / 2 equal magnitudes
     elif k_rank == 2:
         top[:] = rng.uniform(3.0, 4.0, k).astype(np.float32)
-    rest = rng.uniform(0.9, 0.99, listed).astype(np.float32)
+    rest = rng.uniform(0.95, 0.99, listed).astype(np.float32)  # listed by either call, whose bounds differ
     if k_rank == 1:
         rest[: listed // 2] = np.float32(1.03)
     vals = np.concatenate([top, rest]) * rng.choice(np.float32([-1.0, 1.0]), k + listed)
@@ -556,9 +556,12 @@ def test_hinted_select_at_its_limits(variant, listed, k_rank, k):
     res = np.zeros(N, np.float32)
     note(f"hinted select limits listed={listed} k_rank={k_rank} variant={variant}")
     sp = make(N, variant)
+    # the select enqueued with the step, or the passes where it does not apply
+    passes = int(k_rank == 2 or k + listed > max(16 * k, 1 << 18))
     for _ in range(2):
         topk_vs_oracle(g, res, 0, 1, (k + 0.5) / N, variant, sp=sp, hint=1.0)
         assert sp.last_topk_route() == micro.MICRO_TOPK_ROUTE_HINT_LIST
+        assert sp.last_topk_passes() == passes
     sp.close()
 
 
@@ -577,6 +580,8 @@ def test_hinted_trim_of_long_lists(listed):
     sp = make(N, AUTO)
     for _ in range(2):
         topk_vs_oracle(g, np.zeros(N, np.float32), 0, 1, (k + 0.5) / N, AUTO, sp=sp, hint=1.0)
+        assert (sp.last_topk_route(), sp.last_topk_passes()) == (micro.MICRO_TOPK_ROUTE_HINT_LIST, 0)
+    sp.close()
 
 
 def test_bound_of_the_hint_after_quiet_steps():
