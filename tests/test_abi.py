@@ -276,6 +276,23 @@ def test_noalloc_step_argument_errors_without_device_work():
     assert k.value == 0 and th.value == 1.5
 
 
+@pytest.mark.parametrize("where", [0, 1, 7, 8, 9])
+def test_noalloc_step_takes_addresses_only(where):
+    """Bytes, strings and ctypes objects hold host memory, no device address:
+    refused before the library is called (which would refuse the threshold)."""
+    for wrong in (b"12345678", "12345678", (ctypes.c_float * 8)(), ctypes.pointer(ctypes.c_float()), 8.0):
+        args = [64, 4096, 8, 0, 1, 0.5, -1.0, 8192, 12288, None]
+        args[where] = wrong
+        with pytest.raises(TypeError):
+            _lib.micro_sparsify_step_noalloc(*args)
+    with pytest.raises(_lib.MicroError) as e:
+        _lib.micro_sparsify_step_noalloc(64, 4096, 8, 0, 1, 0.5, -1.0, 8192, 12288, None)
+    assert e.value.status == _lib.MICRO_EINVAL
+    with pytest.raises(_lib.MicroError) as e:
+        _lib.micro_sparsify_step_noalloc(None, 4096, 8, 0, 1, 0.5, 1.0, 8192, 12288, None)
+    assert e.value.status == _lib.MICRO_EINVAL
+
+
 def test_init_without_device_reports_hip_error():
     import torch
     if torch.cuda.is_available():
