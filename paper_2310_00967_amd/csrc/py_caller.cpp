@@ -11,7 +11,9 @@
 // whose launch and wait take 12.
 #include <Python.h>
 
+#include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
+#include <torch/csrc/utils/object_ptr.h>
 #include <torch/torch.h>
 
 #include <cstdint>
@@ -75,7 +77,29 @@ int64_t partition_length(int64_t n, int64_t rank, int64_t world) {
     return (rank + 1) * n / world - rank * n / world;
 }
 
-PyObject* first(const at::Tensor& t, int64_t k) { return THPVariable_Wrap(t.slice(0, 0, k)); }
+// Views of the first k pairs, or false with the Python error set.
+struct Pairs {
+    THPObjectPtr idx, val;
+    bool make(const Buffers& b, int64_t k) {
+        idx = THPVariable_Wrap(b.idx->slice(0, 0, k));
+        if (!idx.get()) return false;
+        val = THPVariable_Wrap(b.val->slice(0, 0, k));
+        return val.get() != nullptr;
+    }
+};
+
+// A list of n new objects from make(i), or null with the Python error set.
+template <class Make>
+PyObject* list_of(int64_t n, Make make) {
+    THPObjectPtr list(PyList_New(n));
+    if (!list.get()) return nullptr;
+    for (int64_t i = 0; i < n; ++i) {
+        PyObject* item = make(i);
+        if (!item) return nullptr;
+        PyList_SET_ITEM(list.get(), i, item);
+    }
+    return list.release();
+}
 
 // step(grad, residual, rank, world, density, theta, out_idx, out_val)
 PyObject* caller_step(PyObject* self, PyObject* const* args, Py_ssize_t n) {
@@ -83,27 +107,26 @@ PyObject* caller_step(PyObject* self, PyObject* const* args, Py_ssize_t n) {
     int64_t rank, world;
     double density, theta;
     Buffers b;
-    try {
-        if (n != 8 || !integer(args[2], &rank) || !integer(args[3], &world) || world < 1 || world > INT32_MAX ||
-            rank < 0 || rank >= world || !real(args[4], &density) || !real(args[5], &theta) ||
-            !buffers(c, args[0], args[1], args[6], args[7], partition_length(c->n_total, rank, world), &b))
-            Py_RETURN_NONE;
-        const float* grad = static_cast<const float*>(b.grad->data_ptr());
-        float* residual = static_cast<float*>(b.residual->data_ptr());
-        int32_t* idx = static_cast<int32_t*>(b.idx->data_ptr());
-        float* val = static_cast<float*>(b.val->data_ptr());
-        int64_t k = 0;
-        micro_status st;
-        Py_BEGIN_ALLOW_THREADS
-        st = c->step(c->ctx, grad, residual, static_cast<int32_t>(rank), static_cast<int32_t>(world), density, &theta,
-                     idx, val, &k);
-        Py_END_ALLOW_THREADS
-        if (st != MICRO_OK) return PyLong_FromLong(st);
-        return Py_BuildValue("(LdNN)", static_cast<long long>(k), theta, first(*b.idx, k), first(*b.val, k));
-    } catch (const std::exception& e) {
-        PyErr_SetString(PyExc_RuntimeError, e.what());
-        return nullptr;
-    }
+    HANDLE_TH_ERRORS
+    if (n != 8 || !integer(args[2], &rank) || !integer(args[3], &world) || world < 1 || world > INT32_MAX ||
+        rank < 0 || rank >= world || !real(args[4], &density) || !real(args[5], &theta) ||
+        !buffers(c, args[0], args[1], args[6], args[7], partition_length(c->n_total, rank, world), &b))
+        Py_RETURN_NONE;
+    const float* grad = static_cast<const float*>(b.grad->data_ptr());
+    float* residual = static_cast<float*>(b.residual->data_ptr());
+    int32_t* idx = static_cast<int32_t*>(b.idx->data_ptr());
+    float* val = static_cast<float*>(b.val->data_ptr());
+    int64_t k = 0;
+    micro_status st;
+    Py_BEGIN_ALLOW_THREADS
+    st = c->step(c->ctx, grad, residual, static_cast<int32_t>(rank), static_cast<int32_t>(world), density, &theta,
+                 idx, val, &k);
+    Py_END_ALLOW_THREADS
+    if (st != MICRO_OK) return PyLong_FromLong(st);
+    Pairs p;
+    if (!p.make(b, k)) return nullptr;
+    return Py_BuildValue("(LdOO)", static_cast<long long>(k), theta, p.idx.get(), p.val.get());
+    END_HANDLE_TH_ERRORS
 }
 
 // ef_step(grad, residual, t, worker, world, density, theta, out_idx, out_val, local_error)
@@ -112,35 +135,33 @@ PyObject* caller_ef_step(PyObject* self, PyObject* const* args, Py_ssize_t n) {
     int64_t t, worker, world;
     double density, theta, sumsq = 0.0;
     Buffers b;
-    try {
-        if (n != 10 || !integer(args[2], &t) || !integer(args[3], &worker) || !integer(args[4], &world) || t < 0 ||
-            world < 1 || world > INT32_MAX || worker < 0 || worker >= world || !real(args[5], &density) ||
-            !real(args[6], &theta) || !PyBool_Check(args[9]))
-            Py_RETURN_NONE;
-        const int64_t part = (t % world + worker) % world;
-        if (!buffers(c, args[0], args[1], args[7], args[8], partition_length(c->n_total, part, world), &b))
-            Py_RETURN_NONE;
-        const float* grad = static_cast<const float*>(b.grad->data_ptr());
-        float* residual = static_cast<float*>(b.residual->data_ptr());
-        int32_t* idx = static_cast<int32_t*>(b.idx->data_ptr());
-        float* val = static_cast<float*>(b.val->data_ptr());
-        const bool error = args[9] == Py_True;
-        int64_t k = 0;
-        int32_t cycle = 0;
-        micro_status st;
-        Py_BEGIN_ALLOW_THREADS
-        st = c->ef_step(c->ctx, grad, residual, t, static_cast<int32_t>(worker), static_cast<int32_t>(world), density,
-                        &theta, idx, val, &k, &cycle, error ? &sumsq : nullptr);
-        Py_END_ALLOW_THREADS
-        if (st != MICRO_OK) return PyLong_FromLong(st);
-        if (error)
-            return Py_BuildValue("(LdiNNd)", static_cast<long long>(k), theta, cycle, first(*b.idx, k),
-                                 first(*b.val, k), sumsq);
-        return Py_BuildValue("(LdiNN)", static_cast<long long>(k), theta, cycle, first(*b.idx, k), first(*b.val, k));
-    } catch (const std::exception& e) {
-        PyErr_SetString(PyExc_RuntimeError, e.what());
-        return nullptr;
-    }
+    HANDLE_TH_ERRORS
+    if (n != 10 || !integer(args[2], &t) || !integer(args[3], &worker) || !integer(args[4], &world) || t < 0 ||
+        world < 1 || world > INT32_MAX || worker < 0 || worker >= world || !real(args[5], &density) ||
+        !real(args[6], &theta) || !PyBool_Check(args[9]))
+        Py_RETURN_NONE;
+    const int64_t part = (t % world + worker) % world;
+    if (!buffers(c, args[0], args[1], args[7], args[8], partition_length(c->n_total, part, world), &b))
+        Py_RETURN_NONE;
+    const float* grad = static_cast<const float*>(b.grad->data_ptr());
+    float* residual = static_cast<float*>(b.residual->data_ptr());
+    int32_t* idx = static_cast<int32_t*>(b.idx->data_ptr());
+    float* val = static_cast<float*>(b.val->data_ptr());
+    const bool error = args[9] == Py_True;
+    int64_t k = 0;
+    int32_t cycle = 0;
+    micro_status st;
+    Py_BEGIN_ALLOW_THREADS
+    st = c->ef_step(c->ctx, grad, residual, t, static_cast<int32_t>(worker), static_cast<int32_t>(world), density,
+                    &theta, idx, val, &k, &cycle, error ? &sumsq : nullptr);
+    Py_END_ALLOW_THREADS
+    if (st != MICRO_OK) return PyLong_FromLong(st);
+    Pairs p;
+    if (!p.make(b, k)) return nullptr;
+    if (error)
+        return Py_BuildValue("(LdiOOd)", static_cast<long long>(k), theta, cycle, p.idx.get(), p.val.get(), sumsq);
+    return Py_BuildValue("(LdiOO)", static_cast<long long>(k), theta, cycle, p.idx.get(), p.val.get());
+    END_HANDLE_TH_ERRORS
 }
 
 // sweep(grad, residual, world, density, thetas, out_idx, out_val, want_sumsq)
@@ -149,44 +170,36 @@ PyObject* caller_sweep(PyObject* self, PyObject* const* args, Py_ssize_t n) {
     int64_t world, k[kMaxSweepWorld], total = 0;
     double density, theta[kMaxSweepWorld], sumsq[kMaxSweepWorld];
     Buffers b;
-    try {
-        if (n != 8 || !integer(args[2], &world) || world < 1 || world > kMaxSweepWorld || !real(args[3], &density) ||
-            !PyList_CheckExact(args[4]) || PyList_GET_SIZE(args[4]) != world || !PyBool_Check(args[7]))
-            Py_RETURN_NONE;
-        for (int64_t r = 0; r < world; ++r)
-            if (!real(PyList_GET_ITEM(args[4], r), &theta[r])) Py_RETURN_NONE;
-        if (!buffers(c, args[0], args[1], args[5], args[6], c->n_total, &b)) Py_RETURN_NONE;
-        const float* grad = static_cast<const float*>(b.grad->data_ptr());
-        float* residual = static_cast<float*>(b.residual->data_ptr());
-        int32_t* idx = static_cast<int32_t*>(b.idx->data_ptr());
-        float* val = static_cast<float*>(b.val->data_ptr());
-        const bool error = args[7] == Py_True;
-        micro_status st;
-        Py_BEGIN_ALLOW_THREADS
-        st = c->sweep(c->ctx, grad, residual, static_cast<int32_t>(world), density, theta, idx, val, k,
-                      error ? sumsq : nullptr);
-        Py_END_ALLOW_THREADS
-        if (st != MICRO_OK) return PyLong_FromLong(st);
-        PyObject* ks = PyList_New(world);
-        PyObject* ths = PyList_New(world);
-        PyObject* sqs = error ? PyList_New(world) : Py_NewRef(Py_None);
-        if (!ks || !ths || !sqs) {
-            Py_XDECREF(ks);
-            Py_XDECREF(ths);
-            Py_XDECREF(sqs);
-            return PyErr_NoMemory();
-        }
-        for (int64_t r = 0; r < world; ++r) {
-            total += k[r];
-            PyList_SET_ITEM(ks, r, PyLong_FromLongLong(k[r]));
-            PyList_SET_ITEM(ths, r, PyFloat_FromDouble(theta[r]));
-            if (error) PyList_SET_ITEM(sqs, r, PyFloat_FromDouble(sumsq[r]));
-        }
-        return Py_BuildValue("(NNNNN)", ks, ths, sqs, first(*b.idx, total), first(*b.val, total));
-    } catch (const std::exception& e) {
-        PyErr_SetString(PyExc_RuntimeError, e.what());
-        return nullptr;
-    }
+    HANDLE_TH_ERRORS
+    if (n != 8 || !integer(args[2], &world) || world < 1 || world > kMaxSweepWorld || !real(args[3], &density) ||
+        !PyList_CheckExact(args[4]) || PyList_GET_SIZE(args[4]) != world || !PyBool_Check(args[7]))
+        Py_RETURN_NONE;
+    for (int64_t r = 0; r < world; ++r)
+        if (!real(PyList_GET_ITEM(args[4], r), &theta[r])) Py_RETURN_NONE;
+    if (!buffers(c, args[0], args[1], args[5], args[6], c->n_total, &b)) Py_RETURN_NONE;
+    const float* grad = static_cast<const float*>(b.grad->data_ptr());
+    float* residual = static_cast<float*>(b.residual->data_ptr());
+    int32_t* idx = static_cast<int32_t*>(b.idx->data_ptr());
+    float* val = static_cast<float*>(b.val->data_ptr());
+    const bool error = args[7] == Py_True;
+    micro_status st;
+    Py_BEGIN_ALLOW_THREADS
+    st = c->sweep(c->ctx, grad, residual, static_cast<int32_t>(world), density, theta, idx, val, k,
+                  error ? sumsq : nullptr);
+    Py_END_ALLOW_THREADS
+    if (st != MICRO_OK) return PyLong_FromLong(st);
+    for (int64_t r = 0; r < world; ++r) total += k[r];
+    THPObjectPtr ks(list_of(world, [&](int64_t r) { return PyLong_FromLongLong(k[r]); }));
+    if (!ks.get()) return nullptr;
+    THPObjectPtr ths(list_of(world, [&](int64_t r) { return PyFloat_FromDouble(theta[r]); }));
+    if (!ths.get()) return nullptr;
+    THPObjectPtr sqs(error ? list_of(world, [&](int64_t r) { return PyFloat_FromDouble(sumsq[r]); })
+                           : Py_NewRef(Py_None));
+    if (!sqs.get()) return nullptr;
+    Pairs p;
+    if (!p.make(b, total)) return nullptr;
+    return Py_BuildValue("(OOOOO)", ks.get(), ths.get(), sqs.get(), p.idx.get(), p.val.get());
+    END_HANDLE_TH_ERRORS
 }
 
 // Caller(step, ef_step, sweep, ctx, n_total, device): the C functions' and the

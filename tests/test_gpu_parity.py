@@ -4,11 +4,13 @@ Every call goes through the C ABI (include/micro_sparsify.h) via the ctypes
 binding.  Indices, values, the selected count, the next threshold and the
 residual must equal the oracle's bit for bit; the tolerance is zero.
 """
+import gc
 import threading
 
 import numpy as np
 import pytest
 import torch
+from torch.utils._python_dispatch import TorchDispatchMode
 
 import oracle
 import paper_2310_00967_amd as micro
@@ -632,6 +634,45 @@ def test_native_and_python_marshalling_agree():
     sp.close()
     with pytest.raises(RuntimeError):
         sp.step(g, r, 0, world, 0.01, 2.4, oi, ov)
+
+
+@pytest.mark.parametrize("fails", [1, 2])
+@pytest.mark.parametrize("entry", ["step", "ef", "sweep"])
+def test_failing_views_raise_their_own_error_and_hold_nothing(entry, fails):
+    """A torch dispatch mode that raises on the first or second view of a
+    call's pairs: the call raises that error, and no view, and with it no
+    buffer, outlives it."""
+    N, world = 1 << 20, 2
+
+    class Refuse(TorchDispatchMode):
+        left = fails
+
+        def __torch_dispatch__(self, func, types, args=(), kwargs=None):
+            if func is torch.ops.aten.slice.Tensor:
+                self.left -= 1
+                if self.left == 0:
+                    raise KeyError("no view")
+            return func(*args, **(kwargs or {}))
+
+    g = torch.randn(N, device=DEV)
+    r = torch.zeros(N, device=DEV)
+    sp = micro.Sparsifier(N, device=DEV)
+    held = []
+    for _ in range(2):
+        oi = torch.empty(N, dtype=torch.int32, device=DEV)
+        ov = torch.empty(N, dtype=torch.float32, device=DEV)
+        with pytest.raises(KeyError, match="no view"), Refuse():
+            if entry == "step":
+                sp.step(g, r, 0, world, 0.01, 2.0, oi, ov)
+            elif entry == "ef":
+                sp.ef_step(g, r, 0, 0, world, 0.01, 2.0, oi, ov)
+            else:
+                sp.sweep(g, r, world, 0.01, [2.0, 2.0], oi, ov)
+        del oi, ov
+        gc.collect()
+        held.append(torch.cuda.memory_allocated())
+    assert held[0] == held[1]
+    sp.close()
 
 
 def test_long_one_pass_steps_on_two_streams_at_once():
