@@ -171,23 +171,22 @@ def micro_sparsify_step(ctx, grad_ptr, residual_ptr, rank, world, density, theta
     return k.value, th.value
 
 
-def _address(p):
-    """A device address as ctypes takes it: an int as it is (a c_void_p of its
-    own costs 0.3 us), None as NULL; a TypeError for anything else, which an
-    argument of type c_void_p would accept with the host address of its bytes."""
-    return p if p.__class__ is int else ctypes.c_void_p(p)
-
-
 def micro_sparsify_step_noalloc(grad_ptr, residual_ptr, n_total, rank, world, density, theta, out_idx_ptr,
                                 out_val_ptr, stream_handle=None, cfg=None):
     """Raw call of the allocation-free step with device addresses on the
     current device; returns (k, theta_next)."""
     th = ctypes.c_double(float(theta))
     k = ctypes.c_int64()
-    st = load().micro_sparsify_step_noalloc(_address(grad_ptr), _address(residual_ptr), int(n_total), int(rank),
-                                            int(world), float(density), ctypes.byref(th), _address(out_idx_ptr),
-                                            _address(out_val_ptr), ctypes.byref(k), _address(stream_handle or 0),
-                                            ctypes.byref(cfg) if cfg is not None else None)
+    stream = stream_handle or 0
+    if not (grad_ptr.__class__ is residual_ptr.__class__ is out_idx_ptr.__class__ is out_val_ptr.__class__
+            is stream.__class__ is int):
+        # NULL for None; a TypeError for anything else that is no address, which
+        # an argument of type c_void_p would accept with the host address of its bytes
+        grad_ptr, residual_ptr, out_idx_ptr, out_val_ptr, stream = map(
+            ctypes.c_void_p, (grad_ptr, residual_ptr, out_idx_ptr, out_val_ptr, stream))
+    st = load().micro_sparsify_step_noalloc(grad_ptr, residual_ptr, int(n_total), int(rank), int(world),
+                                            float(density), ctypes.byref(th), out_idx_ptr, out_val_ptr,
+                                            ctypes.byref(k), stream, ctypes.byref(cfg) if cfg is not None else None)
     check(st)
     return k.value, th.value
 
