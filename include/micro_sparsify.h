@@ -119,7 +119,9 @@ typedef enum micro_status {
                                   pairs in local memory and places them in the
                                   same single launch; both scratch sets         */
 #define MICRO_VARIANT_TICKET 1 /* one pass, one launch: each tile's offset by
-                                  decoupled look-back, tiles in launch order     */
+                                  decoupled look-back; tiles in launch order up
+                                  to 2^22 values of the partition, drawn from a
+                                  ticket counter above                           */
 #define MICRO_VARIANT_STAGED 2 /* a streaming pass that stages each tile's pairs
                                   (no inter-workgroup waits), a scan pass (look-
                                   back per chunk of a million values) and a
@@ -181,14 +183,15 @@ MICRO_API void micro_config_default(micro_config *cfg);
  * NULL means the null stream).  cfg == NULL selects the defaults.
  * The context owns its device scratch (STAGED: a 256-pair staging slot and a
  * count per 1024 values of the vector plus look-back words, about 2 bytes per
- * value; TICKET: one look-back word per 4096 values and a few; AUTO: both) and a pinned host word
+ * value; TICKET: one look-back word per 4096 values and a few, 1026 tile claims
+ * and a ticket counter; AUTO: both, and 1 KB of mapped host memory) and a pinned host word
  * for the selected count; it never owns the caller's buffers.
  * Returns MICRO_EINVAL (ctx NULL, n_total < 0, bad cfg), MICRO_ERANGE
  * (n_total > INT32_MAX: indices are int32), MICRO_EHIP (no usable device) or
  * MICRO_ENOMEM.  On failure *ctx is set to NULL.  Every context also holds
  * the top-k comparator's 8 KB of radix-select counters and 64 bytes of mapped
- * host memory, and one of MICRO_RULE_TOPK another 90 KB and one byte per 128
- * values of the vector.
+ * host memory, and one of MICRO_RULE_TOPK another 25 KB of counters and one
+ * byte of look-back words per 128 values of the vector, at least 1 KB.
  */
 MICRO_API micro_status micro_sparsify_init(micro_ctx **ctx, int64_t n_total,
                                  void *hip_stream, const micro_config *cfg);

@@ -264,6 +264,13 @@ uint32_t move_grid(int64_t tiles, int64_t len, int64_t span, int64_t min_blocks)
     return static_cast<uint32_t>(blocks < 1 ? 1 : blocks);
 }
 
+// Largest sweep, in scan chunks of a million values, whose stream and scan
+// passes run as one launch.  Measured on MI355X (device time per sweep, fused
+// against separate, same box): ResNet-18's 16 partitions (16 chunks) 43.6
+// against 46.9 us, ResNet-50's 8 (32 chunks) 72.4-73.2 against 72.2 us,
+// BERT-large's 8 (320 chunks) 665-667 against 655-657 us.
+constexpr int64_t kFusedSweepMaxChunks = 64;
+
 // Items per move piece.  The merged sequence holds one item per tile and one
 // per selected value, about tiles + density * values of them.  A long
 // sequence (at least two kMoveSpan-item pieces per compute unit) takes
@@ -277,13 +284,6 @@ uint32_t move_grid(int64_t tiles, int64_t len, int64_t span, int64_t min_blocks)
 // ResNet-50 rank 0 (3.2M values, d = 0.001, about 6,300 items) 26.5%, 27.0%
 // and 27.3%; the GPT-1.3B partition's move kernel took 53 us with 4096-item
 // pieces and 78 us with 2048 (an earlier build of the kernel).
-// Largest sweep, in scan chunks of a million values, whose stream and scan
-// passes run as one launch.  Measured on MI355X (device time per sweep, fused
-// against separate, same box): ResNet-18's 16 partitions (16 chunks) 43.6
-// against 46.9 us, ResNet-50's 8 (32 chunks) 72.4-73.2 against 72.2 us,
-// BERT-large's 8 (320 chunks) 665-667 against 655-657 us.
-constexpr int64_t kFusedSweepMaxChunks = 64;
-
 uint32_t move_span_for(const micro_ctx* ctx, int64_t tiles, double expected_pairs) {
     const double items = static_cast<double>(tiles) + expected_pairs;
     if (items >= 2.0 * ctx->compute_units * micro::kMoveSpan) return micro::kMoveSpan;
@@ -425,12 +425,6 @@ uint32_t topk_blocks(const micro_ctx* ctx, int64_t n, int64_t values_per_thread)
     return static_cast<uint32_t>(std::max<int64_t>(blocks, 1));
 }
 
-// The incoming theta as a hint for this step's k-th magnitude: the step
-// first runs at 1 - slack times it, rounded down to binary32 (*key: its
-// bits).  Taken when theta is positive and finite, 7/8 of it a positive
-// binary32, k at most an eighth of the partition, and the staged scratch
-// there for the trim and the pick.
-
 // The largest binary32 at or below x (x >= 0): FLT_MAX above it.
 float f32_at_or_below(double x) {
     if (x >= static_cast<double>(std::numeric_limits<float>::max())) return std::numeric_limits<float>::max();
@@ -452,6 +446,11 @@ constexpr int64_t kHintedListMin = int64_t(1) << 18;  // taken whatever k is: 64
 // the kernel took 34 us instead of 8.9).
 constexpr int64_t kHintedSmallK = 4096;
 
+// The incoming theta as a hint for this step's k-th magnitude: the step
+// first runs at 1 - slack times it, rounded down to binary32 (*key: its
+// bits).  Taken when theta is positive and finite, 7/8 of it a positive
+// binary32, k at most an eighth of the partition, and the staged scratch
+// there for the trim and the pick.
 bool topk_hint_key(const micro_ctx* ctx, double theta, int64_t k, int64_t len, uint32_t* key) {
     if (!ctx->has_staged || !ctx->d_stage || !ctx->d_tile_counts || !ctx->d_tile_sumsq) return false;
     if (!(theta > 0.0) || !std::isfinite(theta) || k > len / 8) return false;

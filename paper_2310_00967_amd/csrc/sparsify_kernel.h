@@ -29,10 +29,14 @@ static_assert((kMoveSpan & (kMoveSpan - 1)) == 0 && (kMoveSpanSmall & (kMoveSpan
               "piece sizes are powers of two: the kernels divide by them with shifts");
 // One-pass schedule: streaming threads of a workgroup, values per row (one
 // dwordx4 per streaming thread), rows per tile, tiles per look-back group.
-// Rows by partition length, wall time of a step with 1, 4 and 6 rows: 262,144
-// values 18.6, 19.0 and 21.1 us (more workgroups share the load); 730,595
-// values 20.0, 19.6 and 22.7; 3.2M values 30.2, 27.0 and 27.5; 11.7M values
-// 67, 46.1 and 45.6; 41.9M values 209, 120 and 110 (fewer tiles look back).
+// Rows by partition length, wall time of a step with 1, 4 and 6 rows and tiles
+// taken by workgroup index: 262,144 values 18.6, 19.0 and 21.1 us (more
+// workgroups share the load); 730,595 values 20.0, 19.6 and 22.7; 3.2M values
+// 30.2, 27.0 and 27.5 (fewer tiles look back).  With tiles drawn from the ticket
+// counter, four rows and six (the allocation-free step): 3.2M values 33.0 and
+// 30.2 us, 4.3M 39.4 and 35.1, 12M 66.1 and 52.6, 41.9M 162 and 120 (fewer
+// tiles draw, too).  So six rows begin where the claims end: 4,194,304 values
+// take 24.8 us in four-row tiles taken by index, 4,300,000 35.1 in six-row ones.
 constexpr int kPassStream = 256;
 constexpr int kPassRow = kPassStream * 4;
 constexpr int kPassRowsSmall = 1, kPassRowsMid = 4, kPassRowsLarge = 6;
