@@ -1280,7 +1280,7 @@ constexpr uint32_t kPassCap = 1024;                  // pairs a tile stages in L
 // (row, thread, c) sits at base + row * kPassRow + thread * 4 + c, which is
 // also its output order.  Addresses are a uniform base plus a 32-bit offset
 // per thread: 64-bit addresses per value took the four-row kernel to 91
-// vector registers, this form needs 51 (56 with the second bound).
+// vector registers, this form needs 57 (59 with the second bound).
 template <int ROWS>
 struct PassTile {
     int64_t base;      // global index of the tile's first value (uniform)
@@ -1568,10 +1568,12 @@ __device__ __forceinline__ bool absent(const LaunchArgs& a, uint32_t tile) {
 // 119 us, 400M 1.42 and 0.92 ms.
 //
 // Tiles taken by index are claimed by the placing wavefront while the loads are
-// in flight, one word a tile: 262,144 values 16.25 us against 16.4 without
-// claims, ResNet-50 rank 0 24.4 against 24.2, ResNet-18's allocation-free step
-// 20.5 against 20.2; with their tiles drawn from one ticket counter before the
-// loads 19.0, 34.6 and 22.5 us.
+// in flight, one word a tile; the first to need the answer is the tile's count,
+// the others wait for it at the barrier before their stores.  262,144 values
+// 16.3 us and 16.2 without claims, ResNet-50 rank 0 23.8 and 24.4, ResNet-18's
+// allocation-free step 20.3 and 20.6; with every wavefront waiting for the answer at the
+// first barrier 16.3, 24.7 and 20.5, with the tiles drawn from one ticket
+// counter before the loads 19.0, 34.6 and 22.5 us.
 // HINT: only the residual of values at or above theta_zero becomes +0.
 template <int ROWS, bool HINT>
 __device__ __forceinline__ void one_pass_tile(const LaunchArgs& a) {
@@ -1606,7 +1608,6 @@ __device__ __forceinline__ void one_pass_tile(const LaunchArgs& a) {
         uint32_t lane_rank[ROWS], row_count[ROWS], row_base[ROWS];
         wave_ranks<4, ROWS>(sel, lane_rank, row_count);
         const uint32_t count = tile_ranks<ROWS, WAVES>(row_count, lane, wave, s_wave_total, row_base);  // barrier 1
-        if (CLAIMED && !s_claimed) return;  // uniform in the workgroup
         // the two placements share no code: what they share would be kept in
         // registers across the barriers (76 instead of 58 with four rows)
         if (count <= kPassCap) {  // uniform
@@ -1622,11 +1623,13 @@ __device__ __forceinline__ void one_pass_tile(const LaunchArgs& a) {
                     }
                 }
             }
-            __syncthreads();  // barrier 2
+            __syncthreads();                    // barrier 2
+            if (CLAIMED && !s_claimed) return;  // uniform in the workgroup
             pass_store<ROWS>(a, t, tid, zero);
             return;
         }
         __syncthreads();  // barrier 2
+        if (CLAIMED && !s_claimed) return;
         pass_store<ROWS>(a, t, tid, zero);
         __syncthreads();  // barrier 3
 #pragma unroll
@@ -1643,13 +1646,19 @@ __device__ __forceinline__ void one_pass_tile(const LaunchArgs& a) {
         }
         return;
     }
-    if (CLAIMED && lane == 0) s_claimed = claim_tile(a, tile);  // while the tile's loads are in flight
+    // Claimed while the tile's loads are in flight.  Where a waiting workgroup
+    // has taken the tile over, its values may be new ones already: nothing made
+    // of them leaves the workgroup.
+    const bool won = !CLAIMED || (lane == 0 && claim_tile(a, tile));
     __syncthreads();  // barrier 1
-    if (CLAIMED && !s_claimed) return;  // a waiting workgroup has taken the tile over
     const uint32_t part = lane < ROWS * WAVES ? s_wave_total[lane] : 0u;
     const uint32_t count = wave_sum(part);
-    if (lane == 0) publish_pass_tile(a, tile, count);
+    if (lane == 0) {
+        if (CLAIMED) s_claimed = won;
+        if (won) publish_pass_tile(a, tile, count);
+    }
     __syncthreads();  // barrier 2: the pairs are in LDS
+    if (CLAIMED && __ballot(won) == 0) return;
     uint32_t excl;
     if constexpr (CLAIMED) {
         uint32_t patience = kPassPatience;
