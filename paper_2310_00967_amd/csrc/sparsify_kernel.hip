@@ -1581,12 +1581,12 @@ __device__ __forceinline__ void one_pass_tile(const LaunchArgs& a) {
     constexpr int32_t TILE = ROWS * kPassRow;
     __shared__ uint32_t s_wave_total[ROWS * WAVES];
     __shared__ uint2 s_pair[kPassCap];  // (index, value bits)
+    constexpr bool CLAIMED = ROWS != kPassRowsLarge;
     __shared__ uint32_t s_exclusive;
+    __shared__ uint32_t s_claimed;
     const uint32_t tid = threadIdx.x;
     const int lane = tid & (kWaveSize - 1);
     const int wave = __builtin_amdgcn_readfirstlane(tid / kWaveSize);
-    __shared__ uint32_t s_claimed;
-    constexpr bool CLAIMED = ROWS != kPassRowsLarge;
     uint32_t tile = blockIdx.x;
     if constexpr (CLAIMED) {
         if (absent(a, tile)) return;

@@ -732,7 +732,7 @@ __device__ __forceinline__ uint32_t hinted_lookback(const uint64_t* status, uint
 }
 
 // Launch 3, bound by the scattered residual stores and the look-back (BERT-large
-// rank 3's list 10.4 us, where the four launches of the trim took 25.4 us and
+// rank 3's list 11.8 us, where the four launches of the trim took 25.4 us and
 // the gaps between them).  A chunk's entries are all in registers, index and value, before
 // its counts are published (the wait and the barrier below), and a chunk
 // stores only once the counts of every chunk before it are published, to
